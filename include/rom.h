@@ -274,7 +274,7 @@ rom_status rom_destroy(rom_ctx *ctx);
  * rom_last_schedule: the schedule of the context's last FP32-state rank-2
  * run; after an FP64-state run ROM_SCHEDULE_PANEL (panel schedule),
  * ROM_SCHEDULE_RESIDENT (FP64 resident kernel) or -1 (vector-ALU column
- * blocks); -1 if none.  rom_schedule_times: the table's per-step times
+ * blocks, or the FP64 row-split kernels); -1 if none.  rom_schedule_times: the table's per-step times
  * (microseconds) of each schedule for the context's shape at M samples,
  * negative where a schedule does not apply; ROM_E_ARG if that shape is not
  * in the table.
@@ -412,8 +412,16 @@ rom_status rom_run_rank1_batch(rom_ctx *ctx, int32_t M, const double *mu, int64_
  * (the panel schedule where the LDS-resident kernels stop); BF16 / FP8
  * operators with FP32 states within their kernels' LDS limits
  * (ROM_E_UNSUPPORTED above).
- * Errors: ROM_E_ARG, ROM_E_UNSUPPORTED, ROM_E_NOMEM (panel workspace),
- * ROM_E_DEVICE, ROM_E_TIMEOUT.
+ * FP64 states between the resident kernel's sizes and the panel schedule's
+ * (Kv_pad + Ks_pad < 768, max(Kv_pad, Ks_pad) in [128, 512]) run on FP64
+ * row-split kernels: groups of 16 samples over the workgroups of one XCD,
+ * cooperative, with an operator copy and an exchange workspace of the
+ * context (allocated on the first such run) and in-kernel waits that
+ * rom_check reports.  Under graph capture, with ROM_SCHED_COLUMNS, and
+ * where the chip is not a 256-CU gfx950 they run on the vector-ALU column
+ * blocks.
+ * Errors: ROM_E_ARG, ROM_E_UNSUPPORTED, ROM_E_NOMEM (panel or row-split
+ * workspace), ROM_E_DEVICE, ROM_E_TIMEOUT.
  */
 rom_status rom_run_rank2(rom_ctx *ctx, int32_t M, const double *mu, int64_t n0,
                          int64_t nsteps, void *V, void *S, const void *c, double *J,

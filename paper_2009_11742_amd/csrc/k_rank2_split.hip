@@ -1309,7 +1309,7 @@ hipError_t launch_rank2_split_dual(const void *opv0, const void *ops0, const Ran
 // The schedule needs all 256 workgroups resident at once, one per CU, 32 on
 // each of the 8 XCDs (the group-slot logic counts on it), and cooperative
 // launch support.
-bool rank2_split_device_ok() {
+bool split_chip_ok() {
     int dev = 0, ncu = 0, coop = 0;
     if (hipGetDevice(&dev) != hipSuccess) return false;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
@@ -1317,7 +1317,11 @@ bool rank2_split_device_ok() {
     if (ncu != 256 || !coop) return false;
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, dev) != hipSuccess) return false;
-    if (std::string(prop.gcnArchName).rfind("gfx950", 0) != 0) return false;
+    return std::string(prop.gcnArchName).rfind("gfx950", 0) == 0;
+}
+
+bool rank2_split_device_ok() {
+    if (!split_chip_ok()) return false;
     const size_t lds = rank2_split_lds_bytes();
     for (const void *f : kSplitLpKernels) {
         int nb = 0;

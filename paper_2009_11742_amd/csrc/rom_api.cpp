@@ -135,6 +135,7 @@ void free_ctx(rom_ctx *c) {
         if (ev) (void)hipEventDestroy(ev);
     for (hipEvent_t &ev : c->rc_ev)
         if (ev) (void)hipEventDestroy(ev);
+    if (c->sp_ev) (void)hipEventDestroy(c->sp_ev);
     hfree(c->rc_ws);
     hfree(c->avs_rm);
     hfree(c->asv_rm);
@@ -273,6 +274,53 @@ rom_status run_panel(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t st) {
     hipError_t e = rom::launch_rank2_panel(ctx->avs_rm, ctx->asv_rm, a, f64, ctx->pn_ws, st);
     if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: panel launch");
     ctx->last_schedule = ROM_SCHEDULE_PANEL;
+    return ROM_OK;
+}
+
+// Whether an FP64-state run may take the FP64 row-split kernels.
+bool split64_candidate(rom_ctx *ctx, hipStream_t st) {
+    if (!rom::rank2_split64_applies(ctx->kvp, ctx->ksp) || stream_capturing(st)) return false;
+    if (ctx->sp_ok < 0) ctx->sp_ok = rom::split_chip_ok() && rom::rank2_split64_device_ok() ? 1 : 0;
+    return ctx->sp_ok == 1;
+}
+
+// FP64 row-split run: operator packs and workspace built on first use.  The
+// workspace is the context's, so a run on another stream than the last one's
+// waits for that run.
+rom_status run_split64(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t st) {
+    hipError_t e = hipSuccess;
+    if (!ctx->sp_ws) {
+        const size_t ob = rom::rank2_split64_op_bytes(ctx->kvp, ctx->ksp);
+        const size_t wb = rom::rank2_split64_ws_bytes(ctx->kvp, ctx->ksp);
+        e = hipMalloc(&ctx->avs_sp, ob);
+        if (e == hipSuccess) e = hipMalloc(&ctx->asv_sp, ob);
+        if (e == hipSuccess) e = hipMalloc(&ctx->sp_ws, wb);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->sp_ev, hipEventDisableTiming);
+        if (e == hipSuccess)
+            e = rom::launch_split64_pack(static_cast<const double *>(ctx->avs_cm), ctx->kv, ctx->ks, ctx->kvp,
+                                         ctx->ksp, ctx->avs_sp, st);
+        if (e == hipSuccess)
+            e = rom::launch_split64_pack(static_cast<const double *>(ctx->asv_cm), ctx->ks, ctx->kv, ctx->kvp,
+                                         ctx->ksp, ctx->asv_sp, st);
+        if (e != hipSuccess) {
+            if (ctx->sp_ev) (void)hipEventDestroy(ctx->sp_ev);
+            hfree(ctx->avs_sp); hfree(ctx->asv_sp); hfree(ctx->sp_ws);
+            ctx->avs_sp = ctx->asv_sp = ctx->sp_ws = nullptr;
+            ctx->sp_ev = nullptr;
+            return e == hipErrorOutOfMemory ? fail(ROM_E_NOMEM, "rom_run_rank2: row-split allocation failed")
+                                            : hip_fail(e, "rom_run_rank2: row-split setup");
+        }
+        ctx->sp_ws_bytes = wb;
+    } else if (st != ctx->sp_stream) {
+        e = hipStreamWaitEvent(st, ctx->sp_ev, 0);
+        if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: event");
+    }
+    e = rom::launch_rank2_split64(ctx->avs_sp, ctx->asv_sp, a, ctx->sp_ws, ctx->status, st);
+    if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
+    e = hipEventRecord(ctx->sp_ev, st);
+    if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: event");
+    ctx->sp_stream = st;
+    ctx->last_schedule = -1;
     return ROM_OK;
 }
 
@@ -544,6 +592,7 @@ rom_status build_ctx(const rom_config *cfg, bool skew, const double *sA, const d
         if (e == hipSuccess) e = rom::rank2_valu_configure();
         if (e == hipSuccess) e = rom::rank2_lowp_configure();
         if (e == hipSuccess) e = rom::rank2_split_configure();
+        if (e == hipSuccess) e = rom::rank2_split64_configure();
         if (e == hipSuccess) e = rom::receivers_configure();
         if (e != hipSuccess) { free_ctx(c); return hip_fail(e, (w + ": kernel attributes").c_str()); }
         g_configured = true;
@@ -994,6 +1043,9 @@ rom_status rom_run_rank2(rom_ctx *ctx, int32_t M, const double *mu, int64_t n0, 
         if (!(ctx->flags & ROM_SCHED_COLUMNS) && rom::rank2_resident64_applies(ctx->kvp, ctx->ksp, ctx->skew)) {
             e = rom::launch_rank2_resident64(a, ctx->skew, st);
             ctx->last_schedule = ROM_SCHEDULE_RESIDENT;
+        } else if (!(ctx->flags & ROM_SCHED_COLUMNS) && split64_candidate(ctx, st)) {
+            // the sizes between: the FP64 row-split kernels
+            return run_split64(ctx, a, st);
         } else {
             e = rom::launch_rank2_valu<double>(a, st);
             ctx->last_schedule = -1;

@@ -78,6 +78,10 @@ struct rom_ctx {
     void *sp_ws = nullptr;
     size_t sp_ws_bytes = 0;
     int sp_ok = -1;
+    // Last use of sp_ws by an FP64 row-split run: its stream and an event
+    // behind it, so that a run on another stream waits for it.
+    hipStream_t sp_stream = nullptr;
+    hipEvent_t sp_ev = nullptr;
     // Operator-resident schedule (skew FP32 pairs, Kv, Ks <= 256): Avs in
     // the per-thread tile order of its kernel, built by rom_create.
     void *res_pk = nullptr;
@@ -165,6 +169,22 @@ hipError_t launch_rank2_resident(const Rank2Args &a, hipStream_t st);
 // a.asv = the column-major FP64 operators).
 bool rank2_resident64_applies(int kvp, int ksp, bool skew);
 hipError_t launch_rank2_resident64(const Rank2Args &a, bool skew, hipStream_t st);
+
+// FP64 states: the row-split schedule between the resident and the panel
+// kernels' sizes (max(Kv_pad, Ks_pad) in 128 .. 512; a 256-CU gfx950;
+// cooperative launch, not for graph capture).  opv / ops: packs of Avs and
+// Asv, rank2_split64_op_bytes each; ws: rank2_split64_ws_bytes.
+bool rank2_split64_applies(int kvp, int ksp);
+bool rank2_split64_device_ok();
+hipError_t rank2_split64_configure();
+size_t rank2_split64_op_bytes(int kvp, int ksp);
+size_t rank2_split64_ws_bytes(int kvp, int ksp);
+hipError_t launch_split64_pack(const double *A, int rows, int cols, int kvp, int ksp, void *dst, hipStream_t st);
+hipError_t launch_rank2_split64(const void *opv, const void *ops, const Rank2Args &a, void *ws, int *status,
+                                hipStream_t st);
+// Whether the current device is the 256-CU gfx950 with cooperative launches
+// that the row-split kernels count on.
+bool split_chip_ok();
 
 // Rank-1 formulation of M samples in one launch (a.avs / a.asv the
 // column-major FP32 operators, kv, ks <= 1024).
