@@ -223,11 +223,21 @@ rom_status rom_destroy(rom_ctx *ctx);
  *   ROM_SCHEDULE_ROWSPLIT  operator rows split over the workgroups of a
  *                          sample group (16, 32 or 64 samples, see
  *                          ROM_SCHED_ROWSPLIT), kept in registers or
- *                          streamed per quarter, rows exchanged at a group
- *                          barrier every half-step;
+ *                          streamed per quarter, rows exchanged through
+ *                          polled slots or per-wave flags every half-step;
  *   ROM_SCHEDULE_COLUMNS8  as COLUMNS4 with 8 samples per workgroup (FP32
  *                          operators): half the operator bytes per flop,
  *                          half the workgroups.  Bitwise equal to COLUMNS4.
+ *                          With FP32 operators and max(Kv_pad, Ks_pad) in
+ *                          [192, 1024], and all samples on the chip at
+ *                          once, an unpinned and uncaptured run of either
+ *                          takes row-split kernels that keep the operators
+ *                          in registers and compute the same sums: states
+ *                          bitwise equal, J and y too up to Kv_pad = 256,
+ *                          above to FP64 rounding.  They are cooperative, with an exchange workspace of
+ *                          the context (without memory for it the column
+ *                          blocks run) and in-kernel waits that rom_check
+ *                          reports;
  *   ROM_SCHEDULE_RESIDENT  skew pairs (Asv == -Avs^T exactly, the energy-
  *                          conserving structure of Sec. 3.1) with FP32
  *                          operators and Kv, Ks <= 256: one sample per
@@ -258,7 +268,7 @@ rom_status rom_destroy(rom_ctx *ctx);
  * Without a ROM_SCHED_* flag the first run of each shape (Kv_pad, Ks_pad, M
  * rounded up to 64, operator type) times every schedule that applies for 32
  * steps on scratch states and keeps the fastest for the process (that run
- * synchronises the stream; a row-split timing run whose group barrier timed
+ * synchronises the stream; a row-split timing run whose group exchange timed
  * out counts as not applicable, and its status is cleared), unless the process-wide tuning table already
  * holds the shape.  A stream being captured into a graph is never tuned and
  * never takes ROWSPLIT (whatever the flags or the table say): it runs the
@@ -274,8 +284,8 @@ rom_status rom_destroy(rom_ctx *ctx);
  * rom_last_schedule: the schedule of the context's last FP32-state rank-2
  * run; after an FP64-state run ROM_SCHEDULE_PANEL (panel schedule),
  * ROM_SCHEDULE_RESIDENT (FP64 resident kernel) or -1 (vector-ALU column
- * blocks, or the FP64 row-split kernels); -1 if none.  rom_schedule_times: the table's per-step times
- * (microseconds) of each schedule for the context's shape at M samples,
+ * blocks, or the FP64 row-split kernels); -1 if none.  rom_schedule_times: the
+ * table's per-step times (microseconds) of each schedule for the context's shape at M samples,
  * negative where a schedule does not apply; ROM_E_ARG if that shape is not
  * in the table.
  *
@@ -313,7 +323,7 @@ void rom_tune_clear(void);
 
 /*
  * Report in-kernel failures of the work enqueued so far: synchronises
- * `stream`, returns ROM_E_TIMEOUT if a row-split run's group barrier ran out
+ * `stream`, returns ROM_E_TIMEOUT if a row-split run's group exchange ran out
  * of time (its results are then invalid; the kernel still ended), and clears
  * the condition.  ROM_OK otherwise.
  */
@@ -322,7 +332,7 @@ rom_status rom_check(rom_ctx *ctx, void *stream);
 /*
  * Test hook for the failure handling above (not for production use): with
  * on != 0, every later row-split launch of this process waits at its first
- * group barrier for one arrival more than the group has, with a short poll
+ * group exchange for data that no workgroup sends, with a short poll
  * budget, so the wait runs out, ROM_E_TIMEOUT is recorded and every later
  * wait of that launch returns at once; the kernel ends normally with
  * invalid results.  on = 0 restores normal waits.  Process-wide; returns
@@ -416,7 +426,8 @@ rom_status rom_run_rank1_batch(rom_ctx *ctx, int32_t M, const double *mu, int64_
  * (Kv_pad + Ks_pad < 768, max(Kv_pad, Ks_pad) in [128, 512]) run on FP64
  * row-split kernels: groups of 16 samples over the workgroups of one XCD,
  * cooperative, with an operator copy and an exchange workspace of the
- * context (allocated on the first such run) and in-kernel waits that
+ * context (allocated on the first such run; without the memory for them the
+ * vector-ALU column blocks run) and in-kernel waits that
  * rom_check reports.  Under graph capture, with ROM_SCHED_COLUMNS, and
  * where the chip is not a 256-CU gfx950 they run on the vector-ALU column
  * blocks.
@@ -435,11 +446,11 @@ rom_status rom_run_rank2(rom_ctx *ctx, int32_t M, const double *mu, int64_t n0,
  * rom_run_rank2 that takes ROWSPLIT), without allocating, tuning or
  * synchronising.
  *
- * Its scratch (exchange rows, probe partials, barrier counters) lives in a
- * static device array of 8448 KiB per GPU, held until the process ends and
+ * Its scratch (exchange rows, probe partials, flags) lives in a
+ * static device array of 18560 KiB per GPU, held until the process ends and
  * shared by every call on that GPU: calls that overlap on one GPU (several
  * streams, threads or contexts at once) race and give wrong results; calls
- * in stream order are safe (each clears its counters before it runs).  The
+ * in stream order are safe (each clears what it uses before it runs).  The
  * context's row-split operators are prepared by rom_create.  Requires FP32
  * states, Kv == Ks, a padded K the row-split schedule takes (F32 operators:
  * a multiple of 64 in [128, 2048]; BF16 or F8E4M3: a multiple of 128 in
@@ -447,7 +458,7 @@ rom_status rom_run_rank2(rom_ctx *ctx, int32_t M, const double *mu, int64_t n0,
  * ceil(M / 64) groups of 64 samples in one launch (at most 8 floor(32 /
  * (K / 64))) and a 256-CU gfx950: else ROM_E_UNSUPPORTED,
  * as for a scratch need above the static size (nothing enqueued).  A group
- * barrier that timed out is reported by rom_check.  The launch is
+ * exchange that timed out is reported by rom_check.  The launch is
  * cooperative and is not for graph capture.
  * Errors: ROM_E_ARG, ROM_E_UNSUPPORTED, ROM_E_DEVICE.
  */
@@ -480,12 +491,13 @@ rom_status rom_run_rank2_noalloc(rom_ctx *ctx, int32_t M, const double *mu, int6
  * FP32 states and operators.  The forward sweep runs on the schedule a
  * rom_run_rank2 of the same shape takes; when that is ROWSPLIT the call
  * synchronises `stream` after it and returns ROM_E_TIMEOUT (nothing of the
- * reverse sweep enqueued) if one of its group barriers timed out.  With
- * checkpoints and a ROWSPLIT forward sweep, the recompute and reverse sweep
- * of every segment run on the row-split kernels as well, one after the
+ * reverse sweep enqueued) if one of its group exchanges timed out.  With
+ * checkpoints and a ROWSPLIT forward sweep, or a column-block one of a shape
+ * whose unpinned runs take the row-split kernels (ROM_SCHEDULE_COLUMNS8),
+ * the recompute and reverse sweep of every segment run on the row-split kernels as well, one after the
  * other on `stream` (the context then also keeps row-split packs of Asv^T
  * and Avs^T, 2 K^2 floats), the call synchronises `stream` at its end and
- * returns ROM_E_TIMEOUT if a group barrier of those sweeps timed out.
+ * returns ROM_E_TIMEOUT if a group exchange of those sweeps timed out.
  * Otherwise the recompute of the next segment runs on an internal stream
  * beside the reverse sweep on `stream`.  The gradient products of a
  * reversed segment run on a second internal stream; the context keeps the
@@ -518,7 +530,9 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
  *   stats    dev, nsteps x R x 5 FP64 (mean, variance, p5, p50, p95), or
  *            NULL
  *
- * FP32 states and operators only, on the 4-column column-block schedule.
+ * FP32 states and operators only, on the 4-column column-block schedule or
+ * the row-split kernels that compute its sums (ROM_SCHEDULE_COLUMNS8; a wait
+ * of theirs that timed out is reported by rom_check).
  * The run is stepped in chunks whose state traces stay in device memory
  * (up to 2 x 256 MiB of workspace, kept by the context); the seismograms and
  * statistics of a chunk are computed on an internal stream while the next
@@ -597,7 +611,7 @@ rom_status rom_group_destroy(rom_group *g);
  * rom_group_split_k: the smallest padded K of the instances on the plan's
  *   row-split part (every eligible instance with at least that padded K
  *   runs there), 0 for a column-block plan, -1 for NULL.
- * rom_group_check: as rom_check, for the row-split plan's group barriers
+ * rom_group_check: as rom_check, for the row-split plan's group exchanges
  *   (synchronises `stream`).  rom_run_grouped synchronises `stream` after
  *   its run and returns ROM_E_TIMEOUT itself.
  */

@@ -31,6 +31,14 @@
 namespace rom {
 namespace xch {
 
+// Where the rows a wave reads do not fit in its registers at once, polling
+// them one by one would put a branch and a wait into the pipelined loads;
+// there each publishing wave counts its phases in a flag word, stored after
+// its rows' stores have completed, a reader polls the flags of the blocks it
+// needs and then streams the rows unchecked.  (Two buffers would do: whoever
+// publishes phase q has read all of phase q - 1, so every member has read
+// all of phase q - 2.)
+//
 constexpr unsigned kEmpty = 0xFFFFFFFFu;
 constexpr int kRing = 4;
 constexpr long kSpinMax = 1L << 20;   // polls of one bounded wait
@@ -50,7 +58,7 @@ struct Wait {
             __hip_atomic_store(&st[2], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             dead = true;
         } else if ((spins & 63) == 0 &&
-                   __hip_atomic_load(&st[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+                   __builtin_amdgcn_readfirstlane(__hip_atomic_load(&st[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0) {
             dead = true;
         }
         return dead;
@@ -61,6 +69,26 @@ struct Wait {
 // phases ago) complete before anything that follows.
 __device__ __forceinline__ void publish_fence() {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// Poll until the flag words of this lane (null: none) of all lanes of the
+// wave have reached phase `want`.
+__device__ __forceinline__ void wait_flags(Wait &wait, const unsigned *flag, unsigned want) {
+    long spins = 0;
+    for (;;) {
+        bool late = false;
+        if (flag != nullptr)
+            late = (int)(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - want) < 0;
+        if (wait.dead || (!wait.forced && __ballot(late) == 0)) break;
+        if (wait.give_up(spins)) break;
+    }
+    asm volatile("" ::: "memory");
+}
+
+// This wave's rows of a phase are stored: count it (lane 0 of the wave).
+__device__ __forceinline__ void raise_flag(unsigned *flag, unsigned phase) {
+    publish_fence();
+    if ((threadIdx.x & 63) == 0) __hip_atomic_store(flag, phase, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
 __device__ __forceinline__ unsigned max3u(unsigned a, unsigned b, unsigned c) {

@@ -164,6 +164,8 @@ void rank2_split64_kernel(Args64 a) {
             if (wait.dead || (!wait.forced && __ballot(m == xch::kEmpty) == 0)) break;
             if (wait.give_up(spins)) break;
         }
+        // (the emptied slots of the last publication: before the next one)
+        xch::publish_fence();
         d4 acc[NT][CH];
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -230,7 +232,6 @@ void rank2_split64_kernel(Args64 a) {
                 yt += lane::dpp_mov64<lane::kDppXor2>(yt);
                 yt += lane::dpp_mov64<lane::kDppXor1>(yt);
             }
-            xch::publish_fence();
             publish(sv);
             if (probe) publish_y(yt);
             // ---- stress half-step
@@ -242,7 +243,6 @@ void rank2_split64_kernel(Args64 a) {
             // the last stress field is not read; a further group's first
             // publication takes its phase
             if (k + 1 < a.nsteps) {
-                xch::publish_fence();
                 publish(ss);
             }
             // ---- probe: row tile 0 sums the group's partials of this step,

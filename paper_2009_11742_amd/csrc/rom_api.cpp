@@ -148,6 +148,23 @@ bool g_configured = false;
 // Source signal of a context (rom_config flag ROM_SOURCE_GAUSS1).
 int ctx_source(const rom_ctx *c) { return (c->flags & ROM_SOURCE_GAUSS1) ? 1 : 0; }
 
+// Whether the context's device runs the row-split kernels (looked up once per
+// device).
+bool split_device(rom_ctx *ctx) {
+    constexpr int kMax = 64;
+    static std::mutex mu;
+    static int ok[kMax] = {};              // 0 unknown, 1 no, 2 yes
+    if (ctx->sp_ok < 0) {
+        std::lock_guard<std::mutex> lk(mu);
+        const int d = ctx->device;
+        int known = d >= 0 && d < kMax ? ok[d] : 0;
+        if (known == 0) known = rom::rank2_split_device_ok() && rom::rank2_split64_device_ok() ? 2 : 1;
+        if (d >= 0 && d < kMax) ok[d] = known;
+        ctx->sp_ok = known == 2 ? 1 : 0;
+    }
+    return ctx->sp_ok == 1;
+}
+
 // Row-split groups for a rank-2 run of M samples with FP32 states, or 0 if
 // the row-split kernels do not apply (Kv == Ks, padded K a multiple of 64 in
 // [128, 2048] with FP32 operators, a multiple of 128 up to 1024 with BF16 / FP8 ones;
@@ -155,8 +172,7 @@ int ctx_source(const rom_ctx *c) { return (c->flags & ROM_SOURCE_GAUSS1) ? 1 : 0
 int split_candidate(rom_ctx *ctx, int32_t M) {
     const int G = rom::rank2_split_groups(ctx->kv, ctx->ks, ctx->kvp, ctx->ksp, M, ctx->op_type == ROM_F32);
     if (G == 0) return 0;
-    if (ctx->sp_ok < 0) ctx->sp_ok = rom::rank2_split_device_ok() ? 1 : 0;
-    return ctx->sp_ok == 1 ? G : 0;
+    return split_device(ctx) ? G : 0;
 }
 
 // Row-split operator packs of a context (built on first use).
@@ -188,12 +204,19 @@ rom_status prepare_split_pack(rom_ctx *ctx, hipStream_t st) {
     return ROM_OK;
 }
 
-// Row-split operands and workspace of a context (built on first use).
-rom_status prepare_split(rom_ctx *ctx, int G, hipStream_t st) {
-    rom_status rs = prepare_split_pack(ctx, st);
-    if (rs != ROM_OK) return rs;
+// The row-split workspace, at least `need` bytes, for a launch on `st`: it
+// is the context's, so a run on another stream than the last one's waits for
+// that run (sp_done marks its end).
+rom_status take_sp_ws(rom_ctx *ctx, size_t need, hipStream_t st) {
     hipError_t e;
-    const size_t need = rom::rank2_split_workspace_bytes(ctx->kvp, G);
+    if (!ctx->sp_ev) {
+        e = hipEventCreateWithFlags(&ctx->sp_ev, hipEventDisableTiming);
+        if (e != hipSuccess) { ctx->sp_ev = nullptr; return hip_fail(e, "rom_run_rank2: event creation"); }
+        ctx->sp_stream = st;
+    } else if (st != ctx->sp_stream) {
+        e = hipStreamWaitEvent(st, ctx->sp_ev, 0);
+        if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: event");
+    }
     if (ctx->sp_ws_bytes < need) {
         e = hipStreamSynchronize(st);
         if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: synchronize");
@@ -201,10 +224,28 @@ rom_status prepare_split(rom_ctx *ctx, int G, hipStream_t st) {
         ctx->sp_ws = nullptr;
         ctx->sp_ws_bytes = 0;
         e = hipMalloc(&ctx->sp_ws, need);
-        if (e != hipSuccess) { ctx->sp_ws = nullptr; return fail(ROM_E_NOMEM, "rom_run_rank2: workspace allocation failed"); }
+        if (e != hipSuccess) {
+            ctx->sp_ws = nullptr;
+            (void)hipGetLastError();
+            return fail(ROM_E_NOMEM, "rom_run_rank2: workspace allocation failed");
+        }
         ctx->sp_ws_bytes = need;
     }
     return ROM_OK;
+}
+
+rom_status sp_done(rom_ctx *ctx, hipStream_t st) {
+    const hipError_t e = hipEventRecord(ctx->sp_ev, st);
+    if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: event");
+    ctx->sp_stream = st;
+    return ROM_OK;
+}
+
+// Row-split operands and workspace of a context (built on first use).
+rom_status prepare_split(rom_ctx *ctx, int G, hipStream_t st) {
+    rom_status rs = prepare_split_pack(ctx, st);
+    if (rs != ROM_OK) return rs;
+    return take_sp_ws(ctx, rom::rank2_split_workspace_bytes(ctx->kvp, G), st);
 }
 
 // Whether the 8-column blocks apply: FP32 operators and the states of 8
@@ -280,22 +321,15 @@ rom_status run_panel(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t st) {
 // Whether an FP64-state run may take the FP64 row-split kernels.
 bool split64_candidate(rom_ctx *ctx, hipStream_t st) {
     if (!rom::rank2_split64_applies(ctx->kvp, ctx->ksp) || stream_capturing(st)) return false;
-    if (ctx->sp_ok < 0) ctx->sp_ok = rom::split_chip_ok() && rom::rank2_split64_device_ok() ? 1 : 0;
-    return ctx->sp_ok == 1;
+    return split_device(ctx);
 }
 
-// FP64 row-split run: operator packs and workspace built on first use.  The
-// workspace is the context's, so a run on another stream than the last one's
-// waits for that run.
-rom_status run_split64(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t st) {
-    hipError_t e = hipSuccess;
-    if (!ctx->sp_ws) {
+// Operator packs and workspace of an FP64 row-split run, built on first use.
+rom_status prepare_split64(rom_ctx *ctx, hipStream_t st) {
+    if (!ctx->avs_sp) {
         const size_t ob = rom::rank2_split64_op_bytes(ctx->kvp, ctx->ksp);
-        const size_t wb = rom::rank2_split64_ws_bytes(ctx->kvp, ctx->ksp);
-        e = hipMalloc(&ctx->avs_sp, ob);
+        hipError_t e = hipMalloc(&ctx->avs_sp, ob);
         if (e == hipSuccess) e = hipMalloc(&ctx->asv_sp, ob);
-        if (e == hipSuccess) e = hipMalloc(&ctx->sp_ws, wb);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->sp_ev, hipEventDisableTiming);
         if (e == hipSuccess)
             e = rom::launch_split64_pack(static_cast<const double *>(ctx->avs_cm), ctx->kv, ctx->ks, ctx->kvp,
                                          ctx->ksp, ctx->avs_sp, st);
@@ -303,28 +337,53 @@ rom_status run_split64(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t st) {
             e = rom::launch_split64_pack(static_cast<const double *>(ctx->asv_cm), ctx->ks, ctx->kv, ctx->kvp,
                                          ctx->ksp, ctx->asv_sp, st);
         if (e != hipSuccess) {
-            if (ctx->sp_ev) (void)hipEventDestroy(ctx->sp_ev);
-            hfree(ctx->avs_sp); hfree(ctx->asv_sp); hfree(ctx->sp_ws);
-            ctx->avs_sp = ctx->asv_sp = ctx->sp_ws = nullptr;
-            ctx->sp_ev = nullptr;
+            hfree(ctx->avs_sp); hfree(ctx->asv_sp);
+            ctx->avs_sp = ctx->asv_sp = nullptr;
+            (void)hipGetLastError();
             return e == hipErrorOutOfMemory ? fail(ROM_E_NOMEM, "rom_run_rank2: row-split allocation failed")
                                             : hip_fail(e, "rom_run_rank2: row-split setup");
         }
-        ctx->sp_ws_bytes = wb;
-    } else if (st != ctx->sp_stream) {
-        e = hipStreamWaitEvent(st, ctx->sp_ev, 0);
-        if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: event");
     }
-    e = rom::launch_rank2_split64(ctx->avs_sp, ctx->asv_sp, a, ctx->sp_ws, ctx->status, st);
-    if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
-    e = hipEventRecord(ctx->sp_ev, st);
-    if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: event");
-    ctx->sp_stream = st;
-    ctx->last_schedule = -1;
-    return ROM_OK;
+    return take_sp_ws(ctx, rom::rank2_split64_ws_bytes(ctx->kvp, ctx->ksp), st);
 }
 
-rom_status launch_fp32_state_run(rom_ctx *ctx, rom::Rank2Args a, int sched, int G, hipStream_t st) {
+// FP64 row-split run; taken = false, and nothing done, without the memory
+// for its packs and workspace (the column blocks need none).
+rom_status run_split64(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t st, bool &taken) {
+    rom_status rs = prepare_split64(ctx, st);
+    taken = rs != ROM_E_NOMEM;
+    if (rs != ROM_OK) return taken ? rs : ROM_OK;
+    const hipError_t e = rom::launch_rank2_split64(ctx->avs_sp, ctx->asv_sp, a, ctx->sp_ws, ctx->status, st);
+    if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
+    ctx->last_schedule = -1;
+    return sp_done(ctx, st);
+}
+
+// Whether a column-block run of M samples takes the resident row-split
+// kernels, which compute the same sums: FP32 operators, from 192 rows on
+// (below, the whole operator comes through a CU in the time of one
+// exchange: (128, 100), M = 16 2.0 us per step on column blocks, 2.2 split),
+// as long as all groups fit on the chip at once, unless the context pins the
+// column blocks or the stream is being captured, and only with a workspace:
+// without the memory for one the column blocks run.  (Forced time-outs are
+// the row-split schedule's.)
+bool rsplit_columns(rom_ctx *ctx, int M, hipStream_t st) {
+    return ctx->avs_sp && !rom::g_forced_timeout && ctx->op_type == ROM_F32 && ctx->state_type == ROM_F32 &&
+           !(ctx->flags & (ROM_SCHED_COLUMNS | ROM_SCHED_COLUMNS8)) && std::max(ctx->kvp, ctx->ksp) >= 192 &&
+           rom::rank2_rsplit_applies(true, ctx->kv, ctx->ks, ctx->kvp, ctx->ksp, M, 1) && !stream_capturing(st) &&
+           take_sp_ws(ctx, rom::rank2_rsplit_ws_bytes(ctx->kvp, ctx->ksp, M), st) == ROM_OK;
+}
+
+// The column blocks' run on the resident row-split kernels (rsplit_columns).
+rom_status run_rsplit_columns(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t st) {
+    const hipError_t e = rom::launch_rank2_rsplit(true, ctx->avs_sp, ctx->asv_sp, a, ctx->sp_ws, ctx->status, st,
+                                                   a.vtr ? 1 : 0);
+    if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
+    return sp_done(ctx, st);
+}
+
+// timing: a run of the tuner, which compares the schedules' own kernels.
+rom_status launch_fp32_state_run(rom_ctx *ctx, rom::Rank2Args a, int sched, int G, hipStream_t st, bool timing = false) {
     hipError_t e;
     const bool lowp = ctx->op_type == ROM_BF16 || ctx->op_type == ROM_F8E4M3;
     a.single = (lowp && (ctx->flags & ROM_STATE_BF16)) ? 1 : 0;
@@ -338,6 +397,9 @@ rom_status launch_fp32_state_run(rom_ctx *ctx, rom::Rank2Args a, int sched, int 
         if (rs != ROM_OK) return rs;
         e = rom::launch_rank2_split(ctx->avs_sp, ctx->asv_sp, a, lowp ? ctx->op_scale : 1.0f, ctx->sp_ws, G,
                                     ctx->status, !lowp, st);
+        if (e == hipSuccess) return sp_done(ctx, st);
+    } else if (!timing && rsplit_columns(ctx, a.M, st)) {
+        return run_rsplit_columns(ctx, a, st);
     } else if (lowp) {
         a.avs = ctx->avs_lp; a.asv = ctx->asv_lp;
         e = rom::launch_rank2_lowp(a, ctx->op_type, ctx->op_scale, st);
@@ -418,7 +480,7 @@ rom_status time_schedules(rom_ctx *ctx, const rom::Rank2Args &run, unsigned cand
             if (e == hipSuccess && rep > 0) e = hipEventRecord(e0, st);
             if (e != hipSuccess) { rs = hip_fail(e, "schedule tuning"); break; }
             a.nsteps = rep == 0 ? 2 : nsteps;
-            rs = launch_fp32_state_run(ctx, a, sc, G, st);
+            rs = launch_fp32_state_run(ctx, a, sc, G, st, true);
             if (rs != ROM_OK || rep == 0) continue;
             float ms = 0.f;
             e = hipEventRecord(e1, st);
@@ -457,6 +519,15 @@ int fastest(const float (&us)[ROM_NSCHEDULES], unsigned cands = ~0u) {
     return best < 0 ? ROM_SCHEDULE_COLUMNS4 : best;
 }
 
+// Below 320 padded rows the tuner does not choose the row-split schedule for
+// FP32 operators: the column blocks' runs take the same resident row-split
+// kernels there (rsplit_columns), so nothing is to be gained by its other
+// summation order (K = 256, M = 64: 2.04 us per step that way, 1.94 row-split,
+// 4.4 on the column-block kernels that the tuner times).
+unsigned rs_small(const rom_ctx *ctx) {
+    return ctx->op_type == ROM_F32 && ctx->kvp < 320 ? 1u << ROM_SCHEDULE_ROWSPLIT : 0u;
+}
+
 // Schedule of an FP32-state rank-2 run (flags, table, or tuned now).
 // A stream being captured into a graph gets a column-block schedule: the
 // row-split path may allocate its workspace and synchronise, and its
@@ -491,12 +562,12 @@ rom_status pick_schedule(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t st, 
         for (float &u : te.us) u = -1.f;
         rom_status rs = time_schedules(ctx, a, cands, G, kTuneSteps, st, te.us);
         if (rs != ROM_OK) return rs;
-        te.sched = fastest(te.us, cands);
+        te.sched = fastest(te.us, cands & ~rs_small(ctx));
         tune_store(key, te);
     }
     // the table's choice where it applies to this context (a shape's entry
     // is shared by skew and non-skew pairs), else the fastest that does
-    sched = (cands >> te.sched & 1u) ? te.sched : fastest(te.us, cands);
+    sched = (cands >> te.sched & 1u) ? te.sched : fastest(te.us, cands & ~rs_small(ctx));
     return ROM_OK;
 }
 
@@ -659,6 +730,15 @@ rom_status build_ctx(const rom_config *cfg, bool skew, const double *sA, const d
             CHK(rom::launch_resident_pack(static_cast<const float *>(c->avs_cm), kv, ks, c->kvp, c->ksp, c->res_pk,
                                           st), ": pack");
         }
+    }
+    if (c->state_type == ROM_F32 && split_candidate(c, 1) == 0 && !lowp && std::max(c->kvp, c->ksp) >= 192 &&
+        rom::rank2_rsplit_applies(true, kv, ks, c->kvp, c->ksp, 1, 1) && split_device(c)) {
+        // Kv != Ks: the packs of the resident row-split kernels (without the
+        // memory for them the column blocks run)
+        rom_status rs = prepare_split_pack(c, st);
+        if (rs == ROM_E_NOMEM) {
+            (void)hipGetLastError();
+        } else if (rs != ROM_OK) { free_ctx(c); return rs; }
     }
     if (c->state_type == ROM_F32 && split_candidate(c, 1) > 0) {
         // row-split operator packs up front (the allocation-free run needs
@@ -1043,10 +1123,13 @@ rom_status rom_run_rank2(rom_ctx *ctx, int32_t M, const double *mu, int64_t n0, 
         if (!(ctx->flags & ROM_SCHED_COLUMNS) && rom::rank2_resident64_applies(ctx->kvp, ctx->ksp, ctx->skew)) {
             e = rom::launch_rank2_resident64(a, ctx->skew, st);
             ctx->last_schedule = ROM_SCHEDULE_RESIDENT;
-        } else if (!(ctx->flags & ROM_SCHED_COLUMNS) && split64_candidate(ctx, st)) {
-            // the sizes between: the FP64 row-split kernels
-            return run_split64(ctx, a, st);
         } else {
+            // the sizes between: the FP64 row-split kernels
+            if (!(ctx->flags & ROM_SCHED_COLUMNS) && split64_candidate(ctx, st)) {
+                bool taken;
+                const rom_status rs = run_split64(ctx, a, st, taken);
+                if (taken) return rs;
+            }
             e = rom::launch_rank2_valu<double>(a, st);
             ctx->last_schedule = -1;
         }
@@ -1226,7 +1309,14 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
     // row-split variants, one after the other on `stream` (cooperative
     // launches may not share the chip), with the gradient products of each
     // segment on side stream 1 beside the next segment's launches.
-    const bool split_adj = fsched == ROM_SCHEDULE_ROWSPLIT && !rev;
+    // Column-block sweeps that the resident row-split kernels can run take
+    // that path too up to Kv_pad = 256, where the probe, whose trace is the
+    // reverse sweep's amplitude, is summed in the same order as well.
+    const bool pairs = !rev && ctx->kvp <= 256 && (fsched == ROM_SCHEDULE_COLUMNS4 || fsched == ROM_SCHEDULE_COLUMNS8) &&
+                       rsplit_columns(ctx, M, st);
+    const bool split_adj = (fsched == ROM_SCHEDULE_ROWSPLIT && !rev) || pairs;
+    const size_t sp_need = pairs ? rom::rank2_rsplit_ws_bytes(ctx->kvp, ctx->ksp, M)
+                                 : rom::rank2_split_workspace_bytes(ctx->kvp, fG);
     if (split_adj && !ctx->asvT_sp) {
         const size_t pk = sizeof(float) * (size_t)ctx->kvp * ctx->ksp;
         e = hipMalloc(&ctx->asvT_sp, pk);
@@ -1330,9 +1420,25 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
     // reverse sweep and segment g - 1's recompute share a launch (disjoint
     // workgroups, a second workspace); otherwise they run one after the
     // other.
-    bool dual = split_adj && nseg > 1 && rom::rank2_split_dual_width(ctx->kvp, M) >= 0;
+    const bool rdual = rom::rank2_rsplit_applies(pairs, kv, ks, ctx->kvp, ctx->ksp, M, 2);
+    bool dual = split_adj && nseg > 1 && (rdual || (!pairs && rom::rank2_split_dual_width(ctx->kvp, M) >= 0));
+    // one sweep (mode 1 traced, 2 adjoint), or both side by side
+    auto sweep = [&](const void *ov, const void *os, const rom::Rank2Args &r, int mode) {
+        return pairs ? rom::launch_rank2_rsplit(true, ov, os, r, ctx->sp_ws, ctx->status, st, mode)
+                     : rom::launch_rank2_split(ov, os, r, 1.0f, ctx->sp_ws, fG, ctx->status, true, st, mode);
+    };
+    auto both = [&](const rom::Rank2Args &fw, const rom::Rank2Args &bw) {
+        return rdual ? rom::launch_rank2_rsplit_dual(pairs, ctx->avs_sp, ctx->asv_sp, fw, ctx->sp_ws, ctx->asvT_sp,
+                                                     ctx->avsT_sp, bw, ctx->sp_ws2, ctx->status, st)
+                     : rom::launch_rank2_split_dual(ctx->avs_sp, ctx->asv_sp, fw, ctx->sp_ws, ctx->asvT_sp,
+                                                    ctx->avsT_sp, bw, ctx->sp_ws2, fG, ctx->status, st);
+    };
+    if (split_adj) {
+        rom_status rs = take_sp_ws(ctx, sp_need, st);
+        if (rs != ROM_OK) return rs;
+    }
     if (dual) {
-        const size_t need = rom::rank2_split_workspace_bytes(ctx->kvp, fG);
+        const size_t need = sp_need;
         if (ctx->sp_ws2_bytes < need) {
             ACHK(hipStreamSynchronize(st), "rom_adjoint: synchronize");
             hfree(ctx->sp_ws2);
@@ -1349,8 +1455,7 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
     if (split_adj) {
         if (dual) {
             ACHK(load_ckpt(nseg - 1), "rom_adjoint: copy");
-            ACHK(rom::launch_rank2_split(ctx->avs_sp, ctx->asv_sp, split_rec(nseg - 1), 1.0f, ctx->sp_ws, fG,
-                                         ctx->status, true, st, 1), "rom_adjoint: recompute");
+            ACHK(sweep(ctx->avs_sp, ctx->asv_sp, split_rec(nseg - 1), 1), "rom_adjoint: recompute");
         }
         for (int64_t g = nseg - 1; g >= 0; --g) {
             const int b = (int)(g % kTr), bw = (int)(g % kWq);
@@ -1359,18 +1464,14 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
                 const int b1 = (int)((g - 1) % kTr);
                 if (g - 1 + kTr < nseg) ACHK(hipStreamWaitEvent(st, ev_tr_free[b1], 0), "rom_adjoint: event");
                 ACHK(load_ckpt(g - 1), "rom_adjoint: copy");
-                ACHK(rom::launch_rank2_split_dual(ctx->avs_sp, ctx->asv_sp, split_rec(g - 1), ctx->sp_ws,
-                                                  ctx->asvT_sp, ctx->avsT_sp, split_rev(g), ctx->sp_ws2, fG,
-                                                  ctx->status, st), "rom_adjoint: recompute + reverse launch");
+                ACHK(both(split_rec(g - 1), split_rev(g)), "rom_adjoint: recompute + reverse launch");
             } else {
                 if (!dual) {
                     if (g + kTr < nseg) ACHK(hipStreamWaitEvent(st, ev_tr_free[b], 0), "rom_adjoint: event");
                     ACHK(load_ckpt(g), "rom_adjoint: copy");
-                    ACHK(rom::launch_rank2_split(ctx->avs_sp, ctx->asv_sp, split_rec(g), 1.0f, ctx->sp_ws, fG,
-                                                 ctx->status, true, st, 1), "rom_adjoint: recompute");
+                    ACHK(sweep(ctx->avs_sp, ctx->asv_sp, split_rec(g), 1), "rom_adjoint: recompute");
                 }
-                ACHK(rom::launch_rank2_split(ctx->asvT_sp, ctx->avsT_sp, split_rev(g), 1.0f, ctx->sp_ws, fG,
-                                             ctx->status, true, st, 2), "rom_adjoint: reverse launch");
+                ACHK(sweep(ctx->asvT_sp, ctx->avsT_sp, split_rev(g), 2), "rom_adjoint: reverse launch");
             }
             ACHK(hipEventRecord(ev_rev[bw], st), "rom_adjoint: event");
             ACHK(products(g), "rom_adjoint: gradient product");
@@ -1477,6 +1578,7 @@ rom_status rom_run_receivers(rom_ctx *ctx, int32_t M, const double *mu, int64_t 
     a.kv = kv; a.ks = ks; a.kvp = ctx->kvp; a.ksp = ctx->ksp; a.M = M; a.dt = ctx->dt; a.source = ctx_source(ctx);
     a.avs = ctx->avs_pk; a.asv = ctx->asv_pk;
     const int64_t nchunk = (nsteps + L - 1) / L;
+    const bool rsplit = rsplit_columns(ctx, M, st);
     for (int64_t c = 0; c < nchunk; ++c) {
         const int b = (int)(c & 1);
         const int64_t len = std::min<int64_t>(L, nsteps - c * L);
@@ -1484,8 +1586,14 @@ rom_status rom_run_receivers(rom_ctx *ctx, int32_t M, const double *mu, int64_t 
             e = hipStreamWaitEvent(st, ctx->rc_ev[2 + b], 0);
             if (e != hipSuccess) return hip_fail(e, "rom_run_receivers: event");
         }
-        a.n0 = n0 + c * L; a.nsteps = len; a.vtr = vtr[b]; a.str = str[b]; a.y = ysc[b];
-        e = rom::launch_rank2_f32_mfma(a, 1, st);
+        a.n0 = n0 + c * L; a.nsteps = len; a.vtr = vtr[b]; a.str = rsplit ? nullptr : str[b]; a.y = ysc[b];
+        if (rsplit) {
+            rom_status rs = run_rsplit_columns(ctx, a, st);
+            if (rs != ROM_OK) return rs;
+            e = hipSuccess;
+        } else {
+            e = rom::launch_rank2_f32_mfma(a, 1, st);
+        }
         if (e == hipSuccess) e = hipEventRecord(ctx->rc_ev[b], st);
         if (e == hipSuccess) e = hipStreamWaitEvent(s2, ctx->rc_ev[b], 0);
         if (e == hipSuccess)

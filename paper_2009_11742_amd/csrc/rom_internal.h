@@ -78,8 +78,8 @@ struct rom_ctx {
     void *sp_ws = nullptr;
     size_t sp_ws_bytes = 0;
     int sp_ok = -1;
-    // Last use of sp_ws by an FP64 row-split run: its stream and an event
-    // behind it, so that a run on another stream waits for it.
+    // Last use of sp_ws: its stream and an event behind it, so that a run on
+    // another stream waits for it.
     hipStream_t sp_stream = nullptr;
     hipEvent_t sp_ev = nullptr;
     // Operator-resident schedule (skew FP32 pairs, Kv, Ks <= 256): Avs in
@@ -221,8 +221,8 @@ size_t rank2_split_lds_bytes();
 int rank2_split_groups(int kv, int ks, int kvp, int ksp, int M, bool f32);
 bool rank2_split_k_ok(int kvp, bool f32);
 size_t rank2_split_workspace_bytes(int kvp, int G);
-// Workspace of a launch with xfloats exchange floats per field and ypd
-// probe-partial doubles.
+// Workspace of a launch with xfloats exchange words per phase and ypd
+// probe partials per step.
 size_t rank2_split_ws_bytes(size_t xfloats, size_t ypd);
 hipError_t launch_split_pack(const void *lp, bool fp8, int kvp, int ksp, void *dst, hipStream_t st);
 // mode 0: plain run; FP32 only: 1, traced (a.vtr, a.str every step, probe
@@ -240,8 +240,28 @@ int rank2_split_dual_width(int kvp, int M);
 hipError_t launch_rank2_split_dual(const void *opv0, const void *ops0, const Rank2Args &r0, void *ws0,
                                    const void *opv1, const void *ops1, const Rank2Args &r1, void *ws1, int G,
                                    int *status, hipStream_t st);
-size_t rank2_split_f32_lds_bytes();
-// Split-layout FP32 pack of a column-major rows x cols matrix, or with
+// FP32 operators (k_rank2_split_f32.hip): the run, the checks of its kernels.
+hipError_t launch_rank2_split_f32(const void *opv, const void *ops, const Rank2Args &a, void *ws, int G, int *status,
+                                  hipStream_t st, int mode);
+bool rank2_split_f32_device_ok();
+hipError_t rank2_split_f32_configure();
+// Row-split runs with resident operator rows (k_rsplit.h), any Kv, Ks up to
+// 1024: the sums of the row-split schedule, or with `pairs` those of the
+// column blocks, bit for bit.  opv, ops: split packs of Avs (kvp x ksp) and
+// Asv; ws: rank2_rsplit_ws_bytes.  mode 0: plain run; 1: traced (a.vtr, a.str
+// or null, with a.c and a.y); 2: adjoint (as launch_rank2_split).  Dual: r0
+// traced and r1 adjoint side by side.  `runs`: whether that many fit in one
+// launch.  Cooperative; not for graph capture.
+bool rank2_rsplit_applies(bool pairs, int kv, int ks, int kvp, int ksp, int M, int runs);
+size_t rank2_rsplit_ws_bytes(int kvp, int ksp, int M);
+hipError_t launch_rank2_rsplit(bool pairs, const void *opv, const void *ops, const Rank2Args &a, void *ws, int *status,
+                               hipStream_t st, int mode);
+hipError_t launch_rank2_rsplit_dual(bool pairs, const void *opv0, const void *ops0, const Rank2Args &r0, void *ws0,
+                                    const void *opv1, const void *ops1, const Rank2Args &r1, void *ws1, int *status,
+                                    hipStream_t st);
+bool rank2_rsplit_device_ok();
+hipError_t rank2_rsplit_configure();
+// Split-layout FP32 pack (prow pcol floats) of a column-major rows x cols matrix, or with
 // `trans` of the transpose of a column-major cols x rows matrix.
 hipError_t launch_split_pack_f32(const float *A, int rows, int cols, int prow, int pcol, void *dst, hipStream_t st,
                                  bool trans = false);
@@ -279,8 +299,8 @@ hipError_t launch_rank1_step(const void *avs_cm, const void *asv_cm, const void 
 // padded K): one descriptor per 64-sample group.  opv / ops are the
 // instance's row-split FP32 operator packs, b its padded FP32 source, mu /
 // V / S its own arrays (ld kv); the group owns samples col0 .. col0 + 63
-// of the instance's M; xoff is the offset (floats) of its exchange block of
-// 64 kp floats within each field's exchange buffer of the launch.
+// of the instance's M; xoff is the offset (words) of its exchange block of
+// 64 kp words within each of the launch's exchange buffers.
 struct SplitGroup {
     const void *opv, *ops;
     const float *b;
@@ -296,7 +316,7 @@ int rank2_split_groups_per_launch(int kvp);
 // n0.  smap_dev: the launch's slot map, 256 ints, entry 32 xcc + s = 32 lg
 // + r (group g0 + lg, row tile r) for the s-th workgroup on XCD xcc, or -1;
 // every group's kp / 64 row tiles on one XCD.  ws holds
-// rank2_split_ws_bytes(xfloats, 0) bytes (xfloats: the groups' 64 kp
+// rank2_split_ws_bytes(xfloats, 0) bytes (xfloats: the groups' blocks
 // summed); status as for launch_rank2_split.
 hipError_t launch_grouped_split_f32(const SplitGroup *grp_dev, int g0, int G, const int *smap_dev, size_t xfloats,
                                     void *ws, int *status, int64_t n0, int64_t nsteps, hipStream_t st);
