@@ -228,16 +228,21 @@ rom_status rom_destroy(rom_ctx *ctx);
  *   ROM_SCHEDULE_COLUMNS8  as COLUMNS4 with 8 samples per workgroup (FP32
  *                          operators): half the operator bytes per flop,
  *                          half the workgroups.  Bitwise equal to COLUMNS4.
- *                          With FP32 operators and max(Kv_pad, Ks_pad) in
- *                          [192, 1024], and all samples on the chip at
- *                          once, an unpinned and uncaptured run of either
- *                          takes row-split kernels that keep the operators
- *                          in registers and compute the same sums: states
- *                          bitwise equal, J and y too up to Kv_pad = 256,
- *                          above to FP64 rounding.  They are cooperative, with an exchange workspace of
- *                          the context (without memory for it the column
- *                          blocks run) and in-kernel waits that rom_check
- *                          reports;
+ *                          With FP32 operators an unpinned run of either
+ *                          takes faster kernels that compute the same sums
+ *                          where there are some.  Kv_pad, Ks_pad <= 256, not
+ *                          both above 192 nor (256, 192) either way round:
+ *                          one or four samples per workgroup, all of whose
+ *                          32-term chains run side by side; bitwise equal,
+ *                          J and y included.  max(Kv_pad, Ks_pad) in [192,
+ *                          1024], not captured, all samples on the chip at
+ *                          once and that faster: row-split kernels that keep
+ *                          the operators in registers; states bitwise equal,
+ *                          J and y too up to Kv_pad = 256, above to FP64
+ *                          rounding.  These are cooperative, with an
+ *                          exchange workspace of the context (without memory
+ *                          for it the column blocks run) and in-kernel waits
+ *                          that rom_check reports;
  *   ROM_SCHEDULE_RESIDENT  skew pairs (Asv == -Avs^T exactly, the energy-
  *                          conserving structure of Sec. 3.1) with FP32
  *                          operators and Kv, Ks <= 256: one sample per

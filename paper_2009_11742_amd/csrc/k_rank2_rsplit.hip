@@ -1,6 +1,8 @@
 // Launchers of the resident row-split kernels (k_rsplit.h).
 #include "k_rsplit.h"
 
+#include <cmath>
+
 namespace rom {
 namespace {
 
@@ -55,6 +57,11 @@ hipError_t each_kernel(F f) {
 
 bool rank2_rsplit_applies(bool pairs, int kv, int ks, int kvp, int ksp, int M, int runs) {
     return M >= 1 && pick_tile(pairs, kv, ks, kvp, ksp, M, runs) != nullptr;
+}
+
+float rank2_rsplit_us(bool pairs, int kv, int ks, int kvp, int ksp, int M) {
+    const Tile *t = M >= 1 ? pick_tile(pairs, kv, ks, kvp, ksp, M, 1) : nullptr;
+    return t ? t->us : INFINITY;
 }
 
 // (rank2_split_workspace_bytes of the same padded size and 64-column groups

@@ -461,19 +461,22 @@ void rank2_rsplit_kernel(RArgs a0, RArgs a1) {
 
 // Tiles (NCH, NRB, NCB).  NCH = 3, 4 take 32 rows (16 rows would need more
 // than 32 workgroups per group, 64 more registers).
+// us: a step of the largest K of the class with a probe, measured.
 struct Tile {
     int nch, nrb, ncb;
+    float us;
     const void *f[4];          // by Mode
 };
-#define ROM_RT(P, C, B, N)                                                                                          \
-    {C, B, N, {(const void *)rank2_rsplit_kernel<P, C, B, N, kPlain>,                                               \
+#define ROM_RT(P, C, B, N, US)                                                                                      \
+    {C, B, N, US, {(const void *)rank2_rsplit_kernel<P, C, B, N, kPlain>,                                               \
                (const void *)rank2_rsplit_kernel<P, C, B, N, kTraced>,                                              \
                (const void *)rank2_rsplit_kernel<P, C, B, N, kAdjoint>,                                             \
                (const void *)rank2_rsplit_kernel<P, C, B, N, kDual>}}
 #define ROM_RTILES(P)                                                                                               \
-    {ROM_RT(P, 1, 1, 1), ROM_RT(P, 1, 2, 1), ROM_RT(P, 1, 2, 2), ROM_RT(P, 1, 4, 1), ROM_RT(P, 1, 4, 2),            \
-     ROM_RT(P, 2, 1, 1), ROM_RT(P, 2, 2, 1), ROM_RT(P, 2, 1, 2), ROM_RT(P, 2, 2, 2), ROM_RT(P, 2, 4, 1),            \
-     ROM_RT(P, 3, 2, 1), ROM_RT(P, 3, 2, 2), ROM_RT(P, 4, 2, 1), ROM_RT(P, 4, 2, 2)}
+    {ROM_RT(P, 1, 1, 1, 2.4f), ROM_RT(P, 1, 2, 1, 3.3f), ROM_RT(P, 1, 2, 2, 4.0f), ROM_RT(P, 1, 4, 1, 6.5f),        \
+     ROM_RT(P, 1, 4, 2, 6.6f), ROM_RT(P, 2, 1, 1, 3.7f), ROM_RT(P, 2, 2, 1, 6.2f), ROM_RT(P, 2, 1, 2, 6.2f),        \
+     ROM_RT(P, 2, 2, 2, 10.4f), ROM_RT(P, 2, 4, 1, 10.4f), ROM_RT(P, 3, 2, 1, 8.0f), ROM_RT(P, 3, 2, 2, 15.4f),     \
+     ROM_RT(P, 4, 2, 1, 9.0f), ROM_RT(P, 4, 2, 2, 21.2f)}
 constexpr int kTiles = 14;
 extern const Tile kQuarterTiles[kTiles], kPairTiles[kTiles];
 

@@ -359,18 +359,37 @@ rom_status run_split64(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t st, bo
     return sp_done(ctx, st);
 }
 
+// Whether a column-block run takes the small models' kernel, which computes
+// the same sums bit for bit, probe included.
+bool chains(const rom_ctx *ctx, int M) {
+    return ctx->op_type == ROM_F32 && ctx->state_type == ROM_F32 &&
+           !(ctx->flags & (ROM_SCHED_COLUMNS | ROM_SCHED_COLUMNS8)) &&
+           rom::rank2_chains_applies(ctx->kvp, ctx->ksp, M);
+}
+
+// A column-block run (nset column sets), plain or traced, or adjoint sweep;
+// `launches` of them side by side.
+hipError_t launch_columns(const rom_ctx *ctx, const rom::Rank2Args &a, int nset, bool adjoint, hipStream_t st,
+                          int launches = 1) {
+    if (chains(ctx, a.M)) return rom::launch_rank2_chains(a, adjoint, launches, st);
+    return adjoint ? rom::launch_adjoint_f32_mfma(a, st) : rom::launch_rank2_f32_mfma(a, nset, st);
+}
+
 // Whether a column-block run of M samples takes the resident row-split
-// kernels, which compute the same sums: FP32 operators, from 192 rows on
-// (below, the whole operator comes through a CU in the time of one
-// exchange: (128, 100), M = 16 2.0 us per step on column blocks, 2.2 split),
-// as long as all groups fit on the chip at once, unless the context pins the
-// column blocks or the stream is being captured, and only with a workspace:
-// without the memory for one the column blocks run.  (Forced time-outs are
-// the row-split schedule's.)
+// kernels, which compute the same sums: FP32 operators, from 192 rows on,
+// where all groups fit on the chip at once and their measured step is
+// shorter (K = 256, M = 256 2.5 us against 4.6; with M = 700 groups of twice
+// the rows and columns take 5.9), unless the context pins the column blocks
+// or the stream is being captured, and only with a workspace: without the
+// memory for one the column blocks run.  (Forced time-outs are the row-split
+// schedule's.)
 bool rsplit_columns(rom_ctx *ctx, int M, hipStream_t st) {
-    return ctx->avs_sp && !rom::g_forced_timeout && ctx->op_type == ROM_F32 && ctx->state_type == ROM_F32 &&
-           !(ctx->flags & (ROM_SCHED_COLUMNS | ROM_SCHED_COLUMNS8)) && std::max(ctx->kvp, ctx->ksp) >= 192 &&
-           rom::rank2_rsplit_applies(true, ctx->kv, ctx->ks, ctx->kvp, ctx->ksp, M, 1) && !stream_capturing(st) &&
+    if (!ctx->avs_sp || rom::g_forced_timeout || ctx->op_type != ROM_F32 || ctx->state_type != ROM_F32 ||
+        (ctx->flags & (ROM_SCHED_COLUMNS | ROM_SCHED_COLUMNS8)) || std::max(ctx->kvp, ctx->ksp) < 192)
+        return false;
+    const float cols = chains(ctx, M) ? rom::rank2_chains_us(ctx->kvp, ctx->ksp, M)
+                                      : rom::rank2_f32_mfma_us(ctx->kvp, ctx->ksp);
+    return rom::rank2_rsplit_us(true, ctx->kv, ctx->ks, ctx->kvp, ctx->ksp, M) < cols && !stream_capturing(st) &&
            take_sp_ws(ctx, rom::rank2_rsplit_ws_bytes(ctx->kvp, ctx->ksp, M), st) == ROM_OK;
 }
 
@@ -405,7 +424,8 @@ rom_status launch_fp32_state_run(rom_ctx *ctx, rom::Rank2Args a, int sched, int 
         e = rom::launch_rank2_lowp(a, ctx->op_type, ctx->op_scale, st);
     } else {
         a.avs = ctx->avs_pk; a.asv = ctx->asv_pk;
-        e = rom::launch_rank2_f32_mfma(a, sched == ROM_SCHEDULE_COLUMNS8 ? 2 : 1, st);
+        const int nset = sched == ROM_SCHEDULE_COLUMNS8 ? 2 : 1;
+        e = timing ? rom::launch_rank2_f32_mfma(a, nset, st) : launch_columns(ctx, a, nset, false, st);
     }
     if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
     return ROM_OK;
@@ -1368,7 +1388,7 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
         rom::Rank2Args fw = a;
         fw.V = curV; fw.S = curS; fw.J = nullptr; fw.y = ytrb[b]; fw.n0 = nb; fw.nsteps = len;
         fw.vtr = vtrb[b]; fw.str = strb[b];
-        if (r == hipSuccess) r = rom::launch_rank2_f32_mfma(fw, 1, s2);
+        if (r == hipSuccess) r = launch_columns(ctx, fw, 1, false, s2, 2);
         if (r == hipSuccess) r = hipEventRecord(ev_rec[b], s2);
         return r;
     };
@@ -1488,7 +1508,7 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
         rom::Rank2Args ad = a;
         ad.avs = ctx->asvT_pk; ad.asv = ctx->avsT_pk; ad.V = P; ad.S = Q; ad.J = nullptr;
         ad.n0 = nb; ad.nsteps = len; ad.ytr = ytrb[b]; ad.wtr = wtrb[bw]; ad.qtr = qtrb[bw]; ad.dmu = dmu;
-        ACHK(rom::launch_adjoint_f32_mfma(ad, st), "rom_adjoint: reverse launch");
+        ACHK(launch_columns(ctx, ad, 1, true, st, 2), "rom_adjoint: reverse launch");
         ACHK(hipEventRecord(ev_rev[bw], st), "rom_adjoint: event");
         ACHK(products(g), "rom_adjoint: gradient product");
     }
@@ -1592,7 +1612,7 @@ rom_status rom_run_receivers(rom_ctx *ctx, int32_t M, const double *mu, int64_t 
             if (rs != ROM_OK) return rs;
             e = hipSuccess;
         } else {
-            e = rom::launch_rank2_f32_mfma(a, 1, st);
+            e = launch_columns(ctx, a, 1, false, st);
         }
         if (e == hipSuccess) e = hipEventRecord(ctx->rc_ev[b], st);
         if (e == hipSuccess) e = hipStreamWaitEvent(s2, ctx->rc_ev[b], 0);

@@ -190,9 +190,17 @@ bool split_chip_ok();
 // column-major FP32 operators, kv, ks <= 1024).
 hipError_t launch_rank1_batch(const Rank2Args &a, hipStream_t st);
 
+// Small FP32 models (k_rank2_chains.hip): the column blocks' runs, plain or
+// traced (a.vtr), and their adjoint, with the same packs and arguments.
+// rank2_chains_us: a step in us, as measured.
+bool rank2_chains_applies(int kvp, int ksp, int M);
+float rank2_chains_us(int kvp, int ksp, int M);
+hipError_t launch_rank2_chains(const Rank2Args &a, bool adjoint, int launches, hipStream_t st);
+
 // Launchers (return hipSuccess or the launch error).
 hipError_t launch_rank2_f32_mfma(const Rank2Args &a, int nset, hipStream_t st);
 size_t rank2_f32_mfma_lds_bytes(int kvp, int ksp, int nset);
+float rank2_f32_mfma_us(int kvp, int ksp);
 hipError_t launch_adjoint_f32_mfma(const Rank2Args &a, hipStream_t st);
 // The forward steps n0 .. n0 + nsteps - 1 undone from the state after them
 // (a.V, a.S in/out), the state before each step stored at trace entry
@@ -253,6 +261,8 @@ hipError_t rank2_split_f32_configure();
 // traced and r1 adjoint side by side.  `runs`: whether that many fit in one
 // launch.  Cooperative; not for graph capture.
 bool rank2_rsplit_applies(bool pairs, int kv, int ks, int kvp, int ksp, int M, int runs);
+// Its step in us, as measured for the tile it takes; infinity if none fits.
+float rank2_rsplit_us(bool pairs, int kv, int ks, int kvp, int ksp, int M);
 size_t rank2_rsplit_ws_bytes(int kvp, int ksp, int M);
 hipError_t launch_rank2_rsplit(bool pairs, const void *opv, const void *ops, const Rank2Args &a, void *ws, int *status,
                                hipStream_t st, int mode);
