@@ -525,7 +525,7 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
  *   Y[n][r][m] = C[r] . V_m after step n0 + n
  * and over the M samples: mean, population variance (1/M) and the
  * nearest-rank 5th, 50th and 95th percentiles (the ceil(p M / 100)-th
- * smallest value).
+ * smallest value; NaN counts as larger than every number).
  *
  *   M        samples, 1 .. 1024
  *   mu, V, S as rom_run_rank2 (V, S updated in place)

@@ -377,7 +377,7 @@ void rank2_chains_kernel(Rank2Args a) {
     };
     if constexpr (MODE == kTraced) {
         store_v(a.vtr);
-        store_s(a.str);
+        if (a.str) store_s(a.str);
     }
 
     double un[EV];                                        // the next step's amplitudes
@@ -465,7 +465,9 @@ void rank2_chains_kernel(Rank2Args a) {
                 if (a.y && pok) a.y[(size_t)k * M + pm] = y;
             }
         }
-        if constexpr (MODE == kTraced) store_s(a.str + (size_t)(k + 1) * M * ks);
+        if constexpr (MODE == kTraced) {
+            if (a.str) store_s(a.str + (size_t)(k + 1) * M * ks);
+        }
         __syncthreads();
     }
     store_v(static_cast<float *>(a.V));
@@ -513,12 +515,13 @@ float rank2_chains_us(int kvp, int ksp, int M) {
 }
 
 // Arguments as for launch_rank2_f32_mfma (mode 0, traced with a.vtr) and
-// launch_adjoint_f32_mfma (adjoint); launches: how many such run side by side.
+// launch_adjoint_f32_mfma (adjoint), a.str and the
+// probe of a traced run may be null; launches: how many such run side by side.
 hipError_t launch_rank2_chains(const Rank2Args &a, bool adjoint, int launches, hipStream_t st) {
     const Kernel *k = find_kernel(a.kvp, a.ksp);
     if (!k) return hipErrorInvalidValue;
     const bool traced = a.vtr != nullptr;
-    if (adjoint ? !(a.b && a.c && a.ytr && a.qtr && a.wtr) : traced && !a.str) return hipErrorInvalidValue;
+    if (adjoint && !(a.b && a.c && a.ytr && a.qtr && a.wtr)) return hipErrorInvalidValue;
     const int ns = launches * a.M > kOneSample ? 4 : 1;
     const int rv = 64 / k->cv, rs = 64 / k->cs;
     const int wv = (a.kv + rv - 1) / rv, ws = (a.ks + rs - 1) / rs;

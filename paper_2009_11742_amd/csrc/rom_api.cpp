@@ -1556,7 +1556,7 @@ rom_status rom_run_receivers(rom_ctx *ctx, int32_t M, const double *mu, int64_t 
     L = std::max<int64_t>(1, std::min<int64_t>(L, std::min<int64_t>(nsteps, 4096)));
     const size_t n_tr = (size_t)(L + 1) * (kv + ks) * M;              // floats per set: V then S traces
     const size_t n_set = ((n_tr + 3) / 4 * 4 * sizeof(float) + (size_t)L * M * sizeof(double) + 255) / 256 * 256;
-    const size_t bytes = 2 * n_set;
+    const size_t bytes = 2 * n_set + rom::receivers_rows_bytes(kv, R);
     if (!ctx->side[0]) {
         e = hipSuccess;
         for (int i = 0; i < 2 && e == hipSuccess; ++i) e = hipStreamCreateWithFlags(&ctx->side[i], hipStreamNonBlocking);
@@ -1587,18 +1587,19 @@ rom_status rom_run_receivers(rom_ctx *ctx, int32_t M, const double *mu, int64_t 
         str[b] = vtr[b] + (size_t)(L + 1) * kv * M;
         ysc[b] = reinterpret_cast<double *>(base + (n_tr + 3) / 4 * 4 * sizeof(float));
     }
-    // Chunk c is stepped on the caller's stream into trace set c % 2 (the
-    // first receiver row doubles as the stepper's probe, whose trace goes to
-    // scratch), and its seismograms and statistics are taken on the side
+    double *c64 = reinterpret_cast<double *>(static_cast<char *>(ctx->rc_ws) + 2 * n_set);
+    // Chunk c is stepped on the caller's stream into trace set c % 2 (where
+    // the column blocks step it, their traced kernel wants a probe and both
+    // traces: the first receiver row, with its trace in scratch), and its seismograms and statistics are taken on the side
     // stream while the next chunk steps; a set is stepped into again only
     // after the side stream has read it.
     hipStream_t s2 = ctx->side[0];
     rom::Rank2Args a;
-    a.b = ctx->b; a.c = C; a.mu = mu; a.V = V; a.S = S; a.J = nullptr;
+    const bool rsplit = rsplit_columns(ctx, M, st), blocks = !rsplit && !chains(ctx, M);
+    a.b = ctx->b; a.c = blocks ? C : nullptr; a.mu = mu; a.V = V; a.S = S; a.J = nullptr;
     a.kv = kv; a.ks = ks; a.kvp = ctx->kvp; a.ksp = ctx->ksp; a.M = M; a.dt = ctx->dt; a.source = ctx_source(ctx);
     a.avs = ctx->avs_pk; a.asv = ctx->asv_pk;
     const int64_t nchunk = (nsteps + L - 1) / L;
-    const bool rsplit = rsplit_columns(ctx, M, st);
     for (int64_t c = 0; c < nchunk; ++c) {
         const int b = (int)(c & 1);
         const int64_t len = std::min<int64_t>(L, nsteps - c * L);
@@ -1606,7 +1607,7 @@ rom_status rom_run_receivers(rom_ctx *ctx, int32_t M, const double *mu, int64_t 
             e = hipStreamWaitEvent(st, ctx->rc_ev[2 + b], 0);
             if (e != hipSuccess) return hip_fail(e, "rom_run_receivers: event");
         }
-        a.n0 = n0 + c * L; a.nsteps = len; a.vtr = vtr[b]; a.str = rsplit ? nullptr : str[b]; a.y = ysc[b];
+        a.n0 = n0 + c * L; a.nsteps = len; a.vtr = vtr[b]; a.str = blocks ? str[b] : nullptr; a.y = blocks ? ysc[b] : nullptr;
         if (rsplit) {
             rom_status rs = run_rsplit_columns(ctx, a, st);
             if (rs != ROM_OK) return rs;
@@ -1616,8 +1617,9 @@ rom_status rom_run_receivers(rom_ctx *ctx, int32_t M, const double *mu, int64_t 
         }
         if (e == hipSuccess) e = hipEventRecord(ctx->rc_ev[b], st);
         if (e == hipSuccess) e = hipStreamWaitEvent(s2, ctx->rc_ev[b], 0);
+        if (e == hipSuccess && c == 0) e = rom::launch_receiver_rows(static_cast<const float *>(C), R, kv, c64, s2);
         if (e == hipSuccess)
-            e = rom::launch_receivers(vtr[b], kv, M, (int)len, static_cast<const float *>(C), R,
+            e = rom::launch_receivers(vtr[b], kv, M, (int)len, c64, R,
                                       Y ? Y + (size_t)c * L * R * M : nullptr,
                                       stats ? stats + (size_t)c * L * R * 5 : nullptr, s2);
         if (e == hipSuccess) e = hipEventRecord(ctx->rc_ev[2 + b], s2);

@@ -284,7 +284,10 @@ hipError_t rank2_split_static_scratch(int device, void **ptr);
 // Receivers: Y and ensemble statistics of L steps from a chunk's state
 // traces (see k_receivers.hip).
 size_t receivers_lds_bytes(int kv, int M, int R);
-hipError_t launch_receivers(const float *vtr, int kv, int M, int L, const float *C, int R, double *Y,
+// FP64 copy of the receiver rows that launch_receivers reads
+size_t receivers_rows_bytes(int kv, int R);
+hipError_t launch_receiver_rows(const float *C, int R, int kv, double *c64, hipStream_t st);
+hipError_t launch_receivers(const float *vtr, int kv, int M, int L, const double *c64, int R, double *Y,
                             double *stats, hipStream_t st);
 hipError_t receivers_configure();
 bool rank2_split_device_ok();

@@ -121,3 +121,35 @@ def test_receivers_argument_errors():
         assert ei.value.status == code
     assert torch.count_nonzero(V) == 0
     rom.close()
+
+
+@pytest.mark.parametrize("kv,M,R", [(5, 1, 1), (33, 2, 17), (64, 63, 3), (40, 65, 16), (31, 128, 5), (70, 129, 2),
+                                    (100, 257, 31), (32, 513, 15), (65, 1024, 8)])
+def test_receivers_statistics_of_every_size(kv, M, R):
+    """Seismograms against an FP64 product of the trace's states, and the
+    statistics against numpy's of those seismograms, at the edges of the
+    percentile kernel's size classes (values per lane 1 to 16) and of the
+    trace tiles.  Y: an FP64 sum of kv products, 1e-13 of the largest term
+    sum; the percentiles pick one of the values (exact); mean and variance
+    FP64 sums of M values, 1e-13."""
+    from paper_2009_11742_amd import Rom
+    inst = synth.round_to(synth.make_instance(kv, kv, M, seed=kv + M, skew=False), "f32")
+    rom = Rom(inst["Avs"], inst["Asv"], inst["b"], inst["dt"], state="f32")
+    mu = torch.tensor(inst["mu"], dtype=torch.float64, device="cuda")
+    C = np.random.default_rng(kv).standard_normal((R, kv)).astype(np.float32)
+    V, S = rom.zeros(M)
+    V += 1e-2 * torch.tensor(inst["b"], dtype=torch.float32, device="cuda")
+    N = 4
+    o = rom.run_receivers(mu, V, S, N, torch.tensor(C, device="cuda"))
+    rom.check()
+    Y, stats = o["Y"].cpu().numpy(), o["stats"].cpu().numpy()
+    last = C.astype(np.float64) @ V.cpu().numpy().astype(np.float64).T
+    scale = np.abs(C.astype(np.float64)) @ np.abs(V.cpu().numpy().astype(np.float64)).T
+    assert np.all(np.abs(Y[-1] - last) <= 1e-13 * scale)
+    srt = np.sort(Y, axis=2)
+    for i, p in enumerate((5, 50, 95)):
+        assert np.array_equal(stats[:, :, 2 + i], srt[:, :, max(1, -(-p * M // 100)) - 1])
+    top = np.abs(Y).max()
+    assert np.all(np.abs(stats[:, :, 0] - Y.mean(axis=2)) <= 1e-13 * top)
+    assert np.all(np.abs(stats[:, :, 1] - Y.var(axis=2)) <= 1e-13 * top * top)
+    rom.close()
