@@ -41,22 +41,51 @@ __device__ __forceinline__ f4 load_rows4(const float *__restrict__ A, int r, int
     return v;
 }
 
+__host__ __device__ __forceinline__ int tiles_of(int rows, int cols) {
+    return ((rows + kTile - 1) / kTile) * ((cols + kTile - 1) / kTile);
+}
+
+// Up to two products X Y^T over one reduction, in one launch.
+struct Products {
+    const float *X[2], *Y[2];
+    int rows[2], cols[2];
+    int n0;                        // work items of the first
+};
+
 // part[split][col][row] = sum over k in split's range of X[row][k] Y[col][k]
-// for the 64 x 64 output tile (blockIdx.x, blockIdx.y); split = 4 blockIdx.z
-// + wave.  Lane l loads rows r0 + 4 (l % 16) + s (s = 0..3) of reduction
+// for a 64 x 64 output tile; wave w of the workgroup takes a quarter of the
+// split.  Lane l loads rows r0 + 4 (l % 16) + s (s = 0..3) of reduction
 // index k0 + l / 16, which makes s the row phase of four 16-row MFMA A
 // fragments (and likewise four B fragments for the columns): 2 loads feed 16
 // MFMAs.  MFMA output register r of fragment pair (s, s') in lane l is row
-// r0 + 16 (l / 16) + 4 r + s, column c0 + 4 (l % 16) + s'.
+// r0 + 16 (l / 16) + 4 r + s, column c0 + 4 (l % 16) + s'.  The waves'
+// quarters meet in LDS, added in order.
+//
+// Bound by the operands' bytes behind the L2 unless the workgroups of an XCD
+// read the same columns at the same time: workgroup b runs on XCD b % 8, and
+// an XCD takes consecutive work items, the tiles of a split next to each
+// other.  Measured, a segment's two products (512 x 512, 7936 columns): 132
+// us with a split's tiles spread over the XCDs, a launch and 16 partials per
+// product, now 89, and the sum of the partials 4 instead of 27.
+constexpr int kLdT = kTile + 2;
+constexpr size_t kGemmLds = sizeof(double) * 4 * kTile * kLdT;
+
 template <bool VEC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void gemm_nt_mfma_kernel(const float *__restrict__ X, const float *__restrict__ Y, int rows, int cols,
-                         int64_t R, int64_t kper, double *__restrict__ part) {
+void gemm_nt_mfma_kernel(Products pr, int items, int64_t R, int64_t kper, double *__restrict__ part) {
+    extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int li = lane & 15, lk = lane >> 4;
-    const int r0 = blockIdx.x * kTile, c0 = blockIdx.y * kTile;
-    const int split = blockIdx.z * 4 + w;
-    const int64_t kb = (int64_t)split * kper;
+    int it = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (it >= items) return;
+    const int q = it >= pr.n0 ? 1 : 0;
+    if (q) it -= pr.n0;
+    const float *__restrict__ X = pr.X[q], *__restrict__ Y = pr.Y[q];
+    const int rows = pr.rows[q], cols = pr.cols[q];
+    const int tr = (rows + kTile - 1) / kTile, tc = (cols + kTile - 1) / kTile;
+    const int split = it / (tr * tc), tile = it % (tr * tc);
+    const int r0 = tile % tr * kTile, c0 = tile / tr * kTile;
+    const int64_t kb = min((int64_t)(4 * split + w) * kper, R);
     const int64_t ke = kb + kper < R ? kb + kper : R;
     const int rr = r0 + 4 * li, cc = c0 + 4 * li;
     double acc[4][4][4];
@@ -111,21 +140,31 @@ void gemm_nt_mfma_kernel(const float *__restrict__ X, const float *__restrict__ 
 #pragma unroll
                 for (int r = 0; r < 4; ++r) acc[s][t][r] += (double)ch[s][t][r];
     }
-    double *P = part + (size_t)split * rows * cols;
+    double *sm = reinterpret_cast<double *>(smem);
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = r0 + 16 * lk + 4 * r + s, col = cc + t;
-                if (row < rows && col < cols) P[row + (size_t)col * rows] = acc[s][t][r];
-            }
+            for (int r = 0; r < 4; ++r)
+                sm[(size_t)(w * kTile + 4 * li + t) * kLdT + 16 * lk + 4 * r + s] = acc[s][t][r];
+    __syncthreads();
+    double *P = part + (q ? (size_t)(pr.n0 / tiles_of(pr.rows[0], pr.cols[0])) * pr.rows[0] * pr.cols[0] : 0) +
+                (size_t)split * rows * cols;
+    for (int i = threadIdx.x; i < kTile * kTile; i += 256) {
+        const int r = i % kTile, c = i / kTile;
+        const double *d = sm + (size_t)c * kLdT + r;
+        if (r0 + r < rows && c0 + c < cols)
+            P[r0 + r + (size_t)(c0 + c) * rows] = ((d[0] + d[kTile * kLdT]) + d[2 * kTile * kLdT]) + d[3 * kTile * kLdT];
+    }
 }
 
-// dA[i] += alpha * sum_p part[p][i], p = 0 .. nsplit - 1 in order.
-__global__ void reduce_parts_kernel(const double *__restrict__ part, int nsplit, int64_t n, double alpha,
-                                    double *__restrict__ dA) {
+// dA[i] += alpha * sum_p part[p][i], p = 0 .. nsplit - 1 in order, for the
+// launch's products (blockIdx.y).
+__global__ void reduce_parts_kernel(const double *__restrict__ part0, int nsplit, int64_t n, double alpha,
+                                    double *__restrict__ dA0, double *__restrict__ dA1) {
+    const double *part = part0 + (size_t)blockIdx.y * nsplit * n;
+    double *dA = blockIdx.y ? dA1 : dA0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         double v = 0.0;
@@ -182,31 +221,57 @@ int grid_for(int64_t n, int cap) {
 
 }  // namespace
 
-// Workgroups along the reduction: enough tiles x splits to cover the CUs
-// (at most 8, at least 1).
-static int gemm_nt_zsplit(int rows, int cols) {
-    const int tiles = ((rows + kTile - 1) / kTile) * ((cols + kTile - 1) / kTile);
-    int z = (256 + tiles - 1) / tiles;
+// Splits of the reduction: enough tiles x splits to cover the CUs once (at
+// most 8, at least 1).
+static int gemm_nt_zsplit(int rows, int cols, int n) {
+    const int tiles = n * tiles_of(rows, cols);
+    const int z = (256 + tiles - 1) / tiles;
     return z < 1 ? 1 : (z > 8 ? 8 : z);
 }
 
-int gemm_nt_splits(int rows, int cols) { return 4 * gemm_nt_zsplit(rows, cols); }
+size_t gemm_nt_part_doubles(int rows, int cols) {
+    const int z1 = gemm_nt_zsplit(rows, cols, 1), z2 = 2 * gemm_nt_zsplit(rows, cols, 2);
+    return (size_t)(z1 > z2 ? z1 : z2) * rows * cols;
+}
 
-hipError_t launch_gemm_nt_acc64(const float *X, const float *Y, int rows, int cols, int64_t R,
-                                double alpha, double *dA, double *part, hipStream_t st) {
-    if (R <= 0) return hipSuccess;
-    const int z = gemm_nt_zsplit(rows, cols), nsplit = 4 * z;
-    const int64_t kper = ((R + nsplit - 1) / nsplit + 3) / 4 * 4;
-    dim3 grid((rows + kTile - 1) / kTile, (cols + kTile - 1) / kTile, z);
-    if (rows % 4 == 0 && cols % 4 == 0)
-        hipLaunchKernelGGL(gemm_nt_mfma_kernel<true>, grid, dim3(256), 0, st, X, Y, rows, cols, R, kper, part);
+hipError_t launch_gemm_nt_acc64(const GemmNT *p, int n, int64_t R, double alpha, double *part, hipStream_t st) {
+    if (R <= 0 || n <= 0) return hipSuccess;
+    // (both products have the same rows x cols, perhaps transposed)
+    if (n > 2 || (n == 2 && (int64_t)p[0].rows * p[0].cols != (int64_t)p[1].rows * p[1].cols))
+        return hipErrorInvalidValue;
+    const int z = gemm_nt_zsplit(p[0].rows, p[0].cols, n);
+    const int64_t kper = ((R + 4 * z - 1) / (4 * z) + 3) / 4 * 4;
+    Products pr{};
+    bool vec = true;
+    int items = 0;
+    for (int i = 0; i < n; ++i) {
+        pr.X[i] = p[i].X;
+        pr.Y[i] = p[i].Y;
+        pr.rows[i] = p[i].rows;
+        pr.cols[i] = p[i].cols;
+        if (tiles_of(p[i].rows, p[i].cols) != tiles_of(p[0].rows, p[0].cols)) return hipErrorInvalidValue;
+        items += z * tiles_of(p[i].rows, p[i].cols);
+        vec = vec && p[i].rows % 4 == 0 && p[i].cols % 4 == 0;
+    }
+    pr.n0 = items / n;
+    const dim3 grid((items + 7) / 8 * 8);
+    if (vec)
+        hipLaunchKernelGGL(gemm_nt_mfma_kernel<true>, grid, dim3(256), kGemmLds, st, pr, items, R, kper, part);
     else
-        hipLaunchKernelGGL(gemm_nt_mfma_kernel<false>, grid, dim3(256), 0, st, X, Y, rows, cols, R, kper, part);
+        hipLaunchKernelGGL(gemm_nt_mfma_kernel<false>, grid, dim3(256), kGemmLds, st, pr, items, R, kper, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int64_t n = (int64_t)rows * cols;
-    hipLaunchKernelGGL(reduce_parts_kernel, dim3(grid_for(n, 4096)), dim3(256), 0, st, part, nsplit, n, alpha, dA);
+    const int64_t nd = (int64_t)p[0].rows * p[0].cols;
+    hipLaunchKernelGGL(reduce_parts_kernel, dim3(grid_for(nd, 4096), n), dim3(256), 0, st, part, z, nd, alpha, p[0].dA,
+                       n > 1 ? p[1].dA : nullptr);
     return hipGetLastError();
+}
+
+hipError_t gemm_nt_configure() {
+    const hipError_t e = hipFuncSetAttribute((const void *)gemm_nt_mfma_kernel<true>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGemmLds);
+    return e != hipSuccess ? e : hipFuncSetAttribute((const void *)gemm_nt_mfma_kernel<false>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGemmLds);
 }
 
 hipError_t launch_probe_trace(const float *vtr, const float *c, int kv, int M, int64_t len, double *ytr,

@@ -685,6 +685,7 @@ rom_status build_ctx(const rom_config *cfg, bool skew, const double *sA, const d
         if (e == hipSuccess) e = rom::rank2_split_configure();
         if (e == hipSuccess) e = rom::rank2_split64_configure();
         if (e == hipSuccess) e = rom::receivers_configure();
+        if (e == hipSuccess) e = rom::gemm_nt_configure();
         if (e != hipSuccess) { free_ctx(c); return hip_fail(e, (w + ": kernel attributes").c_str()); }
         g_configured = true;
     }
@@ -1230,8 +1231,7 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
     size_t nf = n_ck + kTr * (n_vtr + n_str) + kWq * (n_wtr + n_qtr) + n_cur + n_pq;
     nf = (nf + 3) / 4 * 4;
     const size_t n_ytr = (size_t)C * mK, n_da = 2 * (size_t)kv * ks;
-    const int nsplit = std::max(rom::gemm_nt_splits(kv, ks), rom::gemm_nt_splits(ks, kv));
-    const size_t n_part = (size_t)nsplit * kv * ks;   // gradient-product partials
+    const size_t n_part = rom::gemm_nt_part_doubles(kv, ks);   // gradient-product partials
     const size_t bytes = nf * sizeof(float) + (kTr * n_ytr + n_da + n_part) * sizeof(double);
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e;
@@ -1308,8 +1308,7 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
     for (int64_t g = 0; g < nseg && !rev; ++g) {
         const int64_t nb = g * C, len = (nb + C <= nsteps) ? C : nsteps - nb;
         float *cg = ck + (size_t)g * (v1 + s1);
-        ACHK(hipMemcpyAsync(cg, curV, v1 * 4, hipMemcpyDeviceToDevice, st), "rom_adjoint: checkpoint");
-        ACHK(hipMemcpyAsync(cg + v1, curS, s1 * 4, hipMemcpyDeviceToDevice, st), "rom_adjoint: checkpoint");
+        ACHK(hipMemcpyAsync(cg, curV, (v1 + s1) * 4, hipMemcpyDeviceToDevice, st), "rom_adjoint: checkpoint");
         a.V = curV; a.S = curS; a.J = J; a.n0 = nb; a.nsteps = len;
         rom_status rs = launch_fp32_state_run(ctx, a, fsched, fG, st);
         if (rs != ROM_OK) return rs;
@@ -1327,8 +1326,10 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
     // With a checkpointed forward sweep on the row-split kernels, the
     // recompute and reverse sweeps run on them too: the traced and adjoint
     // row-split variants, one after the other on `stream` (cooperative
-    // launches may not share the chip), with the gradient products of each
-    // segment on side stream 1 beside the next segment's launches.
+    // launches may not share the chip), and so do the gradient products of
+    // each segment (beside the next segment's launch, which needs every CU,
+    // each would wait for the other's workgroups: 437 us per segment of 31
+    // steps at K = 512, M = 256, one after the other 420).
     // Column-block sweeps that the resident row-split kernels can run take
     // that path too up to Kv_pad = 256, where the probe, whose trace is the
     // reverse sweep's amplitude, is summed in the same order as well.
@@ -1381,12 +1382,11 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
             if (r == hipSuccess) r = hipEventRecord(ev_rec[b], s2);
             return r;
         }
-        const float *cg = ck + (size_t)g * (v1 + s1);
-        if (r == hipSuccess) r = hipMemcpyAsync(curV, cg, v1 * 4, hipMemcpyDeviceToDevice, s2);
-        if (r == hipSuccess) r = hipMemcpyAsync(curS, cg + v1, s1 * 4, hipMemcpyDeviceToDevice, s2);
-        // recompute the segment, keeping every state and the probe trace
+        // recompute the segment, keeping every state and the probe trace (in
+        // place: the checkpoint is not needed again)
+        float *cg = ck + (size_t)g * (v1 + s1);
         rom::Rank2Args fw = a;
-        fw.V = curV; fw.S = curS; fw.J = nullptr; fw.y = ytrb[b]; fw.n0 = nb; fw.nsteps = len;
+        fw.V = cg; fw.S = cg + v1; fw.J = nullptr; fw.y = ytrb[b]; fw.n0 = nb; fw.nsteps = len;
         fw.vtr = vtrb[b]; fw.str = strb[b];
         if (r == hipSuccess) r = launch_columns(ctx, fw, 1, false, s2, 2);
         if (r == hipSuccess) r = hipEventRecord(ev_rec[b], s2);
@@ -1400,14 +1400,16 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
     ACHK(hipStreamWaitEvent(s3, ev_fwd, 0), "rom_adjoint: event");
     // gradient products of a reversed segment (side stream 1), then its
     // trace sets are free again
-    auto products = [&](int64_t g) -> hipError_t {
+    auto products = [&](int64_t g, hipStream_t s3) -> hipError_t {
         const int64_t len = (g * C + C <= nsteps) ? C : nsteps - g * C;
         const int b = (int)(g % kTr), bw = (int)(g % kWq);
         // dAvs += dt sum_n W^n (S^n)^T ;  dAsv += dt sum_n Q^{n+1} (V^{n+1})^T
         hipError_t r = hipStreamWaitEvent(s3, ev_rev[bw], 0);
-        if (r == hipSuccess && dAvs) r = rom::launch_gemm_nt_acc64(wtrb[bw], strb[b], kv, ks, len * M, ctx->dt, dAvs64, part, s3);
-        if (r == hipSuccess && dAsv)
-            r = rom::launch_gemm_nt_acc64(qtrb[bw], vtrb[b] + v1, ks, kv, len * M, ctx->dt, dAsv64, part, s3);
+        rom::GemmNT p[2];
+        int np = 0;
+        if (dAvs) p[np++] = {wtrb[bw], strb[b], kv, ks, dAvs64};
+        if (dAsv) p[np++] = {qtrb[bw], vtrb[b] + v1, ks, kv, dAsv64};
+        if (r == hipSuccess) r = rom::launch_gemm_nt_acc64(p, np, len * M, ctx->dt, part, s3);
         if (r == hipSuccess) r = hipEventRecord(ev_tr_free[b], s3);
         if (r == hipSuccess) r = hipEventRecord(ev_wq_free[bw], s3);
         return r;
@@ -1418,7 +1420,8 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
     auto split_rec = [&](int64_t g) {
         const int64_t nb = g * C, len = (nb + C <= nsteps) ? C : nsteps - nb;
         rom::Rank2Args fw = a;
-        fw.V = curV; fw.S = curS; fw.J = nullptr; fw.y = ytrb[g % kTr]; fw.n0 = nb; fw.nsteps = len;
+        float *cg = ck + (size_t)g * (v1 + s1);
+        fw.V = cg; fw.S = cg + v1; fw.J = nullptr; fw.y = ytrb[g % kTr]; fw.n0 = nb; fw.nsteps = len;
         fw.vtr = vtrb[g % kTr]; fw.str = strb[g % kTr];
         return fw;
     };
@@ -1429,12 +1432,6 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
         ad.n0 = nb; ad.nsteps = len; ad.ytr = ytrb[g % kTr]; ad.wtr = wtrb[g % kWq]; ad.qtr = qtrb[g % kWq];
         ad.dmu = dmu;
         return ad;
-    };
-    auto load_ckpt = [&](int64_t g) -> hipError_t {
-        const float *cg = ck + (size_t)g * (v1 + s1);
-        hipError_t r = hipMemcpyAsync(curV, cg, v1 * 4, hipMemcpyDeviceToDevice, st);
-        if (r == hipSuccess) r = hipMemcpyAsync(curS, cg + v1, s1 * 4, hipMemcpyDeviceToDevice, st);
-        return r;
     };
     // Side by side: where two runs of this shape fit one launch, segment g's
     // reverse sweep and segment g - 1's recompute share a launch (disjoint
@@ -1474,7 +1471,6 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
     }
     if (split_adj) {
         if (dual) {
-            ACHK(load_ckpt(nseg - 1), "rom_adjoint: copy");
             ACHK(sweep(ctx->avs_sp, ctx->asv_sp, split_rec(nseg - 1), 1), "rom_adjoint: recompute");
         }
         for (int64_t g = nseg - 1; g >= 0; --g) {
@@ -1483,18 +1479,16 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
             if (dual && g >= 1) {
                 const int b1 = (int)((g - 1) % kTr);
                 if (g - 1 + kTr < nseg) ACHK(hipStreamWaitEvent(st, ev_tr_free[b1], 0), "rom_adjoint: event");
-                ACHK(load_ckpt(g - 1), "rom_adjoint: copy");
                 ACHK(both(split_rec(g - 1), split_rev(g)), "rom_adjoint: recompute + reverse launch");
             } else {
                 if (!dual) {
                     if (g + kTr < nseg) ACHK(hipStreamWaitEvent(st, ev_tr_free[b], 0), "rom_adjoint: event");
-                    ACHK(load_ckpt(g), "rom_adjoint: copy");
                     ACHK(sweep(ctx->avs_sp, ctx->asv_sp, split_rec(g), 1), "rom_adjoint: recompute");
                 }
                 ACHK(sweep(ctx->asvT_sp, ctx->avsT_sp, split_rev(g), 2), "rom_adjoint: reverse launch");
             }
             ACHK(hipEventRecord(ev_rev[bw], st), "rom_adjoint: event");
-            ACHK(products(g), "rom_adjoint: gradient product");
+            ACHK(products(g, st), "rom_adjoint: gradient product");
         }
     }
     if (!split_adj) ACHK(recompute(nseg - 1), "rom_adjoint: recompute");
@@ -1510,7 +1504,7 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
         ad.n0 = nb; ad.nsteps = len; ad.ytr = ytrb[b]; ad.wtr = wtrb[bw]; ad.qtr = qtrb[bw]; ad.dmu = dmu;
         ACHK(launch_columns(ctx, ad, 1, true, st, 2), "rom_adjoint: reverse launch");
         ACHK(hipEventRecord(ev_rev[bw], st), "rom_adjoint: event");
-        ACHK(products(g), "rom_adjoint: gradient product");
+        ACHK(products(g, s3), "rom_adjoint: gradient product");
     }
     // join: nothing of this call stays on the side streams
     ACHK(hipEventRecord(ctx->ev[11], s2), "rom_adjoint: event");
