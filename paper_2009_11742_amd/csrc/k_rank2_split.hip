@@ -107,9 +107,10 @@ constexpr int ring_depth() {
     return polled<KB, NCB>() || KB < d ? KB : d;
 }
 
-template <int KB, bool SINGLE, int NCB>
+template <int KB, bool SINGLE, int NCB, class F>
 __device__ __forceinline__ void products(const u4 (&op)[4][KB], const float *x, unsigned xbytes, int w, int lane,
-                                         const unsigned *flag, unsigned phase, xch::Wait &wait, f4 (&acc)[4][NCB]) {
+                                         const unsigned *flag, unsigned phase, xch::Wait &wait, F &&waited,
+                                         f4 (&acc)[4][NCB]) {
     constexpr int D = ring_depth<KB, SINGLE, NCB>();
 #pragma unroll
     for (int rb = 0; rb < 4; ++rb)
@@ -146,6 +147,7 @@ __device__ __forceinline__ void products(const u4 (&op)[4][KB], const float *x, 
         xch::publish_fence();
     } else {
         xch::wait_flags(wait, flag, phase);
+        waited();
 #pragma unroll
         for (int d = 0; d < D; ++d) load_b<SINGLE, NCB>(xg, kb0 + d, loff, rh[d], rl[d]);
     }
@@ -306,12 +308,17 @@ void rank2_split_kernel(SplitArgs a) {
     auto half_step = [&](int f, const u4 (&op)[4][KB], const double *up, bool forced, bool last,
                          double *ysum) -> double {
         const u64 *yp = yg + (size_t)((ny - 1) & 3) * R * NC + fj;
-        ProbeSum<TPC> ps;
+        // (behind flags the sum follows the wait for them, whose first look
+        // has waited for the partials too: the registers are the products')
+        ProbeSum<TPC, 0, (2 * KB + TPC - 1) / TPC> ps;
         if (ysum) ps.load(yp, NC, R, fs);
+        auto sum = [&] {
+            if (ysum) *ysum = ps.sum(wait, yp, NC, R, fs);
+        };
         f4 acc[4][NCB];
         products<KB, SINGLE, NCB>(op, a.x + (size_t)((q - 1) & 3) * a.xfloats + xoff, 4u * NC * kp, w, lane, flag,
-                                  (unsigned)q, wait, acc);
-        if (ysum) *ysum = ps.sum(wait, yp, NC, R, fs);
+                                  (unsigned)q, wait, sum, acc);
+        if (kPolled) sum();
         float *pw = part + w * NC * kLd;
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb)

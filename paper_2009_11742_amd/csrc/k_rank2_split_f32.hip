@@ -404,8 +404,14 @@ __device__ __forceinline__ void split_f32_run(const SplitArgs &a, int g, int r, 
     auto half_step = [&](int f, const u4 (&res)[KIND > 0 ? KIND : 1][kFrag], const u4 *opt, const double *up, bool forced,
                          bool last, double *ysum) -> double {
         const u64 *yp = yg + (size_t)((ny - 1) & 3) * R * NC + fj;
+        // (behind flags the sum goes ahead of the wait for them: the partials
+        // are a half-step old, and the registers are the products')
         ProbeSum<TPC> ps;
         if (ysum) ps.load(yp, NC, R, fs);
+        auto sum = [&] {
+            if (ysum) *ysum = ps.sum(wait, yp, NC, R, fs);
+        };
+        if (!kPolled) sum();
         double acc[4][NCB][4];
         const float *xb = a.x + (size_t)((q - 1) & 3) * a.xfloats + xoff;
         if constexpr (KIND > 0)
@@ -413,7 +419,7 @@ __device__ __forceinline__ void split_f32_run(const SplitArgs &a, int g, int r, 
         else
             products_stream<-KIND, NCB>(opt + (size_t)w * R * kFrag / kCG * 64, xb, R, w, lane, flag, (unsigned)q, wait,
                                         acc);
-        if (ysum) *ysum = ps.sum(wait, yp, NC, R, fs);
+        if (kPolled) sum();
         double *pf = part + (kTwo ? f * PSZ : 0), *pw = pf + w * NC * kLdD;
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb)

@@ -129,9 +129,10 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
 // ahead of the poll for the rows of the next half-step, so that they cost
 // row tile 0 no trip of their own, and completed (wait) behind it.  All lanes
 // of the wave must call each.
-template <int TPC, int SEQ = 0>
+// NN: partials per thread (at least R / TPC).
+template <int TPC, int SEQ = 0, int NN = 32 / TPC>
 struct ProbeSum {
-    static constexpr int N = 32 / TPC;
+    static constexpr int N = NN;
     u64 v[N];
     __device__ __forceinline__ void load(const u64 *p, int stride, int R, int fs) {
 #pragma unroll
