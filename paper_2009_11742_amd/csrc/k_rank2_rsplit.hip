@@ -59,8 +59,8 @@ bool rank2_rsplit_applies(bool pairs, int kv, int ks, int kvp, int ksp, int M, i
     return M >= 1 && pick_tile(pairs, kv, ks, kvp, ksp, M, runs) != nullptr;
 }
 
-float rank2_rsplit_us(bool pairs, int kv, int ks, int kvp, int ksp, int M) {
-    const Tile *t = M >= 1 ? pick_tile(pairs, kv, ks, kvp, ksp, M, 1) : nullptr;
+float rank2_rsplit_us(bool pairs, int kv, int ks, int kvp, int ksp, int M, int runs) {
+    const Tile *t = M >= 1 ? pick_tile(pairs, kv, ks, kvp, ksp, M, runs) : nullptr;
     return t ? t->us : INFINITY;
 }
 

@@ -389,7 +389,7 @@ bool rsplit_columns(rom_ctx *ctx, int M, hipStream_t st) {
         return false;
     const float cols = chains(ctx, M) ? rom::rank2_chains_us(ctx->kvp, ctx->ksp, M)
                                       : rom::rank2_f32_mfma_us(ctx->kvp, ctx->ksp);
-    return rom::rank2_rsplit_us(true, ctx->kv, ctx->ks, ctx->kvp, ctx->ksp, M) < cols && !stream_capturing(st) &&
+    return rom::rank2_rsplit_us(true, ctx->kv, ctx->ks, ctx->kvp, ctx->ksp, M, 1) < cols && !stream_capturing(st) &&
            take_sp_ws(ctx, rom::rank2_rsplit_ws_bytes(ctx->kvp, ctx->ksp, M), st) == ROM_OK;
 }
 
@@ -1330,10 +1330,16 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
     // each segment (beside the next segment's launch, which needs every CU,
     // each would wait for the other's workgroups: 437 us per segment of 31
     // steps at K = 512, M = 256, one after the other 420).
-    // Column-block sweeps that the resident row-split kernels can run take
+    // Column-block sweeps (also behind an operator-resident forward sweep)
+    // that the resident row-split kernels can run take
     // that path too up to Kv_pad = 256, where the probe, whose trace is the
-    // reverse sweep's amplitude, is summed in the same order as well.
-    const bool pairs = !rev && ctx->kvp <= 256 && (fsched == ROM_SCHEDULE_COLUMNS4 || fsched == ROM_SCHEDULE_COLUMNS8) &&
+    // reverse sweep's amplitude, is summed in the same order as well, and
+    // where two of them side by side gain enough on column blocks, which have
+    // the products beside them (K = 256, us per step of the adjoint: M = 64
+    // 10.0 on column blocks, 8.9 on these; M = 256 9.7 and 11.0).
+    const bool pairs = !rev && ctx->kvp <= 256 && fsched != ROM_SCHEDULE_ROWSPLIT && fsched != ROM_SCHEDULE_PANEL &&
+                       rom::rank2_rsplit_us(true, kv, ks, ctx->kvp, ctx->ksp, M, 2) <
+                           0.6f * rom::rank2_f32_mfma_us(ctx->kvp, ctx->ksp) &&
                        rsplit_columns(ctx, M, st);
     const bool split_adj = (fsched == ROM_SCHEDULE_ROWSPLIT && !rev) || pairs;
     const size_t sp_need = pairs ? rom::rank2_rsplit_ws_bytes(ctx->kvp, ctx->ksp, M)
@@ -1409,7 +1415,14 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
         int np = 0;
         if (dAvs) p[np++] = {wtrb[bw], strb[b], kv, ks, dAvs64};
         if (dAsv) p[np++] = {qtrb[bw], vtrb[b] + v1, ks, kv, dAsv64};
-        if (r == hipSuccess) r = rom::launch_gemm_nt_acc64(p, np, len * M, ctx->dt, part, s3);
+        // (one after the other beside the next segment's sweeps, which leave
+        // CUs free; in turn with them both at once)
+        if (split_adj) {
+            if (r == hipSuccess) r = rom::launch_gemm_nt_acc64(p, np, len * M, ctx->dt, part, s3);
+        } else {
+            for (int i = 0; i < np && r == hipSuccess; ++i)
+                r = rom::launch_gemm_nt_acc64(p + i, 1, len * M, ctx->dt, part, s3);
+        }
         if (r == hipSuccess) r = hipEventRecord(ev_tr_free[b], s3);
         if (r == hipSuccess) r = hipEventRecord(ev_wq_free[bw], s3);
         return r;

@@ -268,7 +268,7 @@ hipError_t rank2_split_f32_configure();
 // launch.  Cooperative; not for graph capture.
 bool rank2_rsplit_applies(bool pairs, int kv, int ks, int kvp, int ksp, int M, int runs);
 // Its step in us, as measured for the tile it takes; infinity if none fits.
-float rank2_rsplit_us(bool pairs, int kv, int ks, int kvp, int ksp, int M);
+float rank2_rsplit_us(bool pairs, int kv, int ks, int kvp, int ksp, int M, int runs);
 size_t rank2_rsplit_ws_bytes(int kvp, int ksp, int M);
 hipError_t launch_rank2_rsplit(bool pairs, const void *opv, const void *ops, const Rank2Args &a, void *ws, int *status,
                                hipStream_t st, int mode);
