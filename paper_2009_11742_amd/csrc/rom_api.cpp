@@ -1368,7 +1368,13 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
     // sweep done; ev[1 + i] trace set i free; ev[4 + i] trace set i
     // recomputed; ev[7 + i] W/Q set i free; ev[9 + i] reverse sweep into W/Q
     // set i done; ev[11], ev[12] side streams drained.
-    hipStream_t s2 = ctx->side[0], s3 = ctx->side[1];
+    // The small models' sweeps, a few us per segment, run on the caller's
+    // stream one after the other: events between streams cost more than what
+    // would run side by side, most of all once the process has launched a
+    // cooperative kernel (K = 43, M = 11, 153 steps: 874 us per call, 3678
+    // then, 1016 on one stream either way).
+    const bool one = !rev && !split_adj && chains(ctx, M);
+    hipStream_t s2 = one ? st : ctx->side[0], s3 = one ? st : ctx->side[1];
     hipEvent_t ev_fwd = ctx->ev[0], *ev_tr_free = ctx->ev + 1, *ev_rec = ctx->ev + 4;
     hipEvent_t *ev_wq_free = ctx->ev + 7, *ev_rev = ctx->ev + 9;
     auto recompute = [&](int64_t g) -> hipError_t {
@@ -1394,7 +1400,7 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
         rom::Rank2Args fw = a;
         fw.V = cg; fw.S = cg + v1; fw.J = nullptr; fw.y = ytrb[b]; fw.n0 = nb; fw.nsteps = len;
         fw.vtr = vtrb[b]; fw.str = strb[b];
-        if (r == hipSuccess) r = launch_columns(ctx, fw, 1, false, s2, 2);
+        if (r == hipSuccess) r = launch_columns(ctx, fw, 1, false, s2, one ? 1 : 2);
         if (r == hipSuccess) r = hipEventRecord(ev_rec[b], s2);
         return r;
     };
@@ -1515,7 +1521,7 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
         rom::Rank2Args ad = a;
         ad.avs = ctx->asvT_pk; ad.asv = ctx->avsT_pk; ad.V = P; ad.S = Q; ad.J = nullptr;
         ad.n0 = nb; ad.nsteps = len; ad.ytr = ytrb[b]; ad.wtr = wtrb[bw]; ad.qtr = qtrb[bw]; ad.dmu = dmu;
-        ACHK(launch_columns(ctx, ad, 1, true, st, 2), "rom_adjoint: reverse launch");
+        ACHK(launch_columns(ctx, ad, 1, true, st, one ? 1 : 2), "rom_adjoint: reverse launch");
         ACHK(hipEventRecord(ev_rev[bw], st), "rom_adjoint: event");
         ACHK(products(g, s3), "rom_adjoint: gradient product");
     }
