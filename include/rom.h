@@ -234,7 +234,7 @@ rom_status rom_destroy(rom_ctx *ctx);
  *                          both above 192 nor (256, 192) either way round:
  *                          one or four samples per workgroup, all of whose
  *                          32-term chains run side by side; bitwise equal,
- *                          J and y included.  max(Kv_pad, Ks_pad) in [192,
+ *                          J and y included.  max(Kv_pad, Ks_pad) in [256,
  *                          1024], not captured, all samples on the chip at
  *                          once and that faster: row-split kernels that keep
  *                          the operators in registers; states bitwise equal,
@@ -344,6 +344,18 @@ rom_status rom_check(rom_ctx *ctx, void *stream);
  * ROM_OK.
  */
 rom_status rom_debug_force_timeout(int32_t on);
+
+/*
+ * Test hook: the kernels that the context's last rom_run_rank2,
+ * rom_run_receivers or rom_adjoint call launched (ROM_KERNEL_* bits; other
+ * kernels have no bit).  0 for NULL.
+ */
+#define ROM_KERNEL_COLUMNS 1u      /* FP32 column blocks */
+#define ROM_KERNEL_CHAINS 2u       /* small FP32 models */
+#define ROM_KERNEL_ROWS 4u         /* resident row-split kernels with the column blocks' sums */
+#define ROM_KERNEL_ROWS64 8u       /* FP64 row-split kernels */
+#define ROM_KERNEL_VALU64 16u      /* FP64 vector-ALU column blocks */
+uint32_t rom_debug_kernels(const rom_ctx *ctx);
 
 /*
  * Test hook for the grouped plans' row-split packing (host logic only; no

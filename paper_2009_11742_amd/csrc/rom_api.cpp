@@ -356,6 +356,7 @@ rom_status run_split64(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t st, bo
     const hipError_t e = rom::launch_rank2_split64(ctx->avs_sp, ctx->asv_sp, a, ctx->sp_ws, ctx->status, st);
     if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
     ctx->last_schedule = -1;
+    ctx->kernels |= ROM_KERNEL_ROWS64;
     return sp_done(ctx, st);
 }
 
@@ -369,15 +370,16 @@ bool chains(const rom_ctx *ctx, int M) {
 
 // A column-block run (nset column sets), plain or traced, or adjoint sweep;
 // `launches` of them side by side.
-hipError_t launch_columns(const rom_ctx *ctx, const rom::Rank2Args &a, int nset, bool adjoint, hipStream_t st,
+hipError_t launch_columns(rom_ctx *ctx, const rom::Rank2Args &a, int nset, bool adjoint, hipStream_t st,
                           int launches = 1) {
+    ctx->kernels |= chains(ctx, a.M) ? ROM_KERNEL_CHAINS : ROM_KERNEL_COLUMNS;
     if (chains(ctx, a.M)) return rom::launch_rank2_chains(a, adjoint, launches, st);
     return adjoint ? rom::launch_adjoint_f32_mfma(a, st) : rom::launch_rank2_f32_mfma(a, nset, st);
 }
 
 // Whether a column-block run of M samples takes the resident row-split
-// kernels, which compute the same sums: FP32 operators, from 192 rows on,
-// where all groups fit on the chip at once and their measured step is
+// kernels, which compute the same sums: FP32 operators, above 192 padded rows
+// (up to there the small models' kernels are faster than any tile), where all groups fit on the chip at once and their measured step is
 // shorter (K = 256, M = 256 2.5 us against 4.6; with M = 700 groups of twice
 // the rows and columns take 5.9), unless the context pins the column blocks
 // or the stream is being captured, and only with a workspace: without the
@@ -385,7 +387,7 @@ hipError_t launch_columns(const rom_ctx *ctx, const rom::Rank2Args &a, int nset,
 // schedule's.)
 bool rsplit_columns(rom_ctx *ctx, int M, hipStream_t st) {
     if (!ctx->avs_sp || rom::g_forced_timeout || ctx->op_type != ROM_F32 || ctx->state_type != ROM_F32 ||
-        (ctx->flags & (ROM_SCHED_COLUMNS | ROM_SCHED_COLUMNS8)) || std::max(ctx->kvp, ctx->ksp) < 192)
+        (ctx->flags & (ROM_SCHED_COLUMNS | ROM_SCHED_COLUMNS8)) || std::max(ctx->kvp, ctx->ksp) <= 192)
         return false;
     const float cols = chains(ctx, M) ? rom::rank2_chains_us(ctx->kvp, ctx->ksp, M)
                                       : rom::rank2_f32_mfma_us(ctx->kvp, ctx->ksp);
@@ -398,6 +400,7 @@ rom_status run_rsplit_columns(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t
     const hipError_t e = rom::launch_rank2_rsplit(true, ctx->avs_sp, ctx->asv_sp, a, ctx->sp_ws, ctx->status, st,
                                                    a.vtr ? 1 : 0);
     if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
+    ctx->kernels |= ROM_KERNEL_ROWS;
     return sp_done(ctx, st);
 }
 
@@ -752,7 +755,7 @@ rom_status build_ctx(const rom_config *cfg, bool skew, const double *sA, const d
                                           st), ": pack");
         }
     }
-    if (c->state_type == ROM_F32 && split_candidate(c, 1) == 0 && !lowp && std::max(c->kvp, c->ksp) >= 192 &&
+    if (c->state_type == ROM_F32 && split_candidate(c, 1) == 0 && !lowp && std::max(c->kvp, c->ksp) > 192 &&
         rom::rank2_rsplit_applies(true, kv, ks, c->kvp, c->ksp, 1, 1) && split_device(c)) {
         // Kv != Ks: the packs of the resident row-split kernels (without the
         // memory for them the column blocks run)
@@ -967,6 +970,8 @@ rom_status rom_debug_force_timeout(int32_t on) {
 
 int32_t rom_last_schedule(rom_ctx *ctx) { return ctx ? ctx->last_schedule : -1; }
 
+uint32_t rom_debug_kernels(const rom_ctx *ctx) { return ctx ? ctx->kernels : 0u; }
+
 rom_status rom_schedule_times(rom_ctx *ctx, int32_t M, double us[ROM_NSCHEDULES]) {
     if (!ctx || M < 1 || !us) return fail(ROM_E_ARG, "rom_schedule_times: bad argument");
     TuneEntry te;
@@ -1101,6 +1106,7 @@ rom_status rom_run_rank2(rom_ctx *ctx, int32_t M, const double *mu, int64_t n0, 
     if (!mu || !V || !S) return fail(ROM_E_ARG, "rom_run_rank2: NULL mu, V or S");
     if (n0 < 0 || nsteps < 0) return fail(ROM_E_ARG, "rom_run_rank2: n0 and nsteps must be >= 0");
     if ((J || y) && !c) return fail(ROM_E_ARG, "rom_run_rank2: J and y require the probe c");
+    ctx->kernels = 0;
     if (nsteps == 0) return ROM_OK;
     rom::Rank2Args a;
     a.b = ctx->b; a.c = c; a.mu = mu; a.V = V; a.S = S; a.J = J; a.y = y;
@@ -1153,6 +1159,7 @@ rom_status rom_run_rank2(rom_ctx *ctx, int32_t M, const double *mu, int64_t n0, 
             }
             e = rom::launch_rank2_valu<double>(a, st);
             ctx->last_schedule = -1;
+            ctx->kernels |= ROM_KERNEL_VALU64;
         }
     }
     if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
@@ -1208,6 +1215,7 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
     if (ctx->kvp + ctx->ksp > rom::kMaxPadSum ||
         rom::rank2_f32_mfma_lds_bytes(ctx->kvp, ctx->ksp, 1) > 160 * 1024)
         return fail(ROM_E_UNSUPPORTED, "rom_adjoint: Kv + Ks above the LDS-resident limit");
+    ctx->kernels = 0;
     // ckpt_stride -1: no checkpoints, the states are recovered by stepping
     // the leapfrog backwards from the final state (segments of sqrt(N) steps)
     const bool rev = ckpt_stride == -1;
@@ -1342,6 +1350,7 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
                            0.6f * rom::rank2_f32_mfma_us(ctx->kvp, ctx->ksp) &&
                        rsplit_columns(ctx, M, st);
     const bool split_adj = (fsched == ROM_SCHEDULE_ROWSPLIT && !rev) || pairs;
+    if (pairs) ctx->kernels |= ROM_KERNEL_ROWS;
     const size_t sp_need = pairs ? rom::rank2_rsplit_ws_bytes(ctx->kvp, ctx->ksp, M)
                                  : rom::rank2_split_workspace_bytes(ctx->kvp, fG);
     if (split_adj && !ctx->asvT_sp) {
@@ -1559,6 +1568,7 @@ rom_status rom_run_receivers(rom_ctx *ctx, int32_t M, const double *mu, int64_t 
         return fail(ROM_E_UNSUPPORTED, "rom_run_receivers: Kv + Ks above the LDS-resident limit");
     if ((int64_t)R * M > 8192 || rom::receivers_lds_bytes(ctx->kv, M, R) > 160 * 1024)
         return fail(ROM_E_UNSUPPORTED, "rom_run_receivers: R x M or R x Kv too large for one workgroup's LDS");
+    ctx->kernels = 0;
     if (nsteps == 0) return ROM_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e;

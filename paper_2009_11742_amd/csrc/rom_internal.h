@@ -88,6 +88,8 @@ struct rom_ctx {
     // Schedule of the last FP32-state rank-2 run (a rom_schedule, -1 none
     // yet).
     int last_schedule = -1;
+    // ROM_KERNEL_* bits of the last rank-2, receiver or adjoint call.
+    uint32_t kernels = 0;
     // Device status words: [0] scratch of rom_create, [1] in-kernel error
     // (ROM_E_TIMEOUT), [2] abort flag of the row-split barriers.
     int *status = nullptr;

@@ -1,0 +1,69 @@
+"""Which kernels a call launches (rom_debug_kernels), so that the tests that
+compare kernels with each other compare what they mean to: the small models'
+kernels, the resident row-split kernels with the column blocks' sums, the FP64
+row-split kernels, and the column blocks where a context pins them.
+"""
+import pytest
+
+import synth
+from paper_2009_11742_amd import _lib
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def columns_table():
+    """The autotuner's table with `columns` for a shape."""
+    from paper_2009_11742_amd import tuning
+    saved = tuning.entries()
+
+    def put(kv, ks, M):
+        up = lambda x: (x + 63) // 64 * 64
+        tuning.put(up(kv), up(ks), up(M), "f32", "columns", [1.0, -1, -1, -1, -1])
+    yield put
+    tuning.clear()
+    for e in saved:
+        tuning.put(e["kv_pad"], e["ks_pad"], e["m_pad"], e["op"], e["schedule"], e["us"])
+
+
+def _launched(kv, ks, M, state, schedule="auto", call="run"):
+    from paper_2009_11742_amd import Rom
+    inst = synth.make_instance(kv, ks, M, seed=1, skew=False)
+    rom = Rom(inst["Avs"], inst["Asv"], inst["b"], inst["dt"], state=state, schedule=schedule)
+    mu = torch.tensor(inst["mu"], dtype=torch.float64, device="cuda")
+    V, S = rom.zeros(M)
+    if call == "run":
+        rom.run_rank2(mu, V, S, 60)
+    else:
+        rom.run_receivers(mu, V, S, 60, torch.ones((2, kv), dtype=torch.float32, device="cuda"))
+    rom.check()
+    k = _lib.load().rom_debug_kernels(rom.handle)
+    rom.close()
+    return k
+
+
+CHAINS = [(1, 1, 1), (64, 63, 257), (113, 128, 1001), (192, 128, 40), (131, 190, 300), (256, 64, 260), (70, 193, 300),
+          # 192 padded rows: no row-split tile is faster
+          (192, 130, 1), (130, 192, 17), (192, 192, 700)]
+ROWS = [(256, 192, 20), (192, 256, 300), (256, 200, 128), (250, 256, 500), (256, 256, 700), (300, 280, 33),
+        (64, 512, 16), (512, 500, 129), (512, 512, 500), (700, 600, 128), (600, 768, 250),
+        (1000, 1024, 100), (1024, 900, 256)]
+BLOCKS = [(512, 40, 250)]       # no tile that holds all its groups is faster
+
+
+@pytest.mark.parametrize("call", ["run", "receivers"])
+@pytest.mark.parametrize("kv,ks,M,kernel", [s + (_lib.ROM_KERNEL_CHAINS,) for s in CHAINS] +
+                         [s + (_lib.ROM_KERNEL_ROWS,) for s in ROWS] + [s + (_lib.ROM_KERNEL_COLUMNS,) for s in BLOCKS])
+def test_column_block_runs(columns_table, kv, ks, M, kernel, call):
+    columns_table(kv, ks, M)
+    assert _launched(kv, ks, M, "f32", call=call) == kernel
+    assert _launched(kv, ks, M, "f32", schedule="columns", call=call) == _lib.ROM_KERNEL_COLUMNS
+
+
+@pytest.mark.parametrize("kv,ks,M", [(128, 128, 1), (130, 70, 17), (70, 180, 16), (512, 64, 5), (64, 512, 33),
+                                     (300, 280, 390), (192, 192, 1100)])
+def test_fp64_runs(kv, ks, M):
+    assert _launched(kv, ks, M, "f64") == _lib.ROM_KERNEL_ROWS64
+    assert _launched(kv, ks, M, "f64", schedule="columns") == _lib.ROM_KERNEL_VALU64
