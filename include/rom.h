@@ -509,11 +509,10 @@ rom_status rom_run_rank2_noalloc(rom_ctx *ctx, int32_t M, const double *mu, int6
  * rom_run_rank2 of the same shape takes; when that is ROWSPLIT the call
  * synchronises `stream` after it and returns ROM_E_TIMEOUT (nothing of the
  * reverse sweep enqueued) if one of its group exchanges timed out.  With
- * checkpoints and a ROWSPLIT forward sweep, or where column-block sweeps are
- * faster on the row-split kernels that compute their sums
- * (ROM_SCHEDULE_COLUMNS8), the recompute and reverse sweep of every segment run on the row-split kernels as well, one after the
- * other on `stream` (the context then also keeps row-split packs of Asv^T
- * and Avs^T, 2 K^2 floats), the call synchronises `stream` at its end and
+ * checkpoints and a ROWSPLIT forward sweep, the recompute and reverse sweep
+ * of every segment run on the row-split kernels as well, one after the other
+ * on `stream` (the context then also keeps row-split packs of Asv^T and
+ * Avs^T, 2 K^2 floats), the call synchronises `stream` at its end and
  * returns ROM_E_TIMEOUT if a group exchange of those sweeps timed out.
  * Otherwise the recompute of the next segment runs on an internal stream
  * beside the reverse sweep on `stream`, and the gradient products of a

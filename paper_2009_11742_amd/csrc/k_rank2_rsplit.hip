@@ -47,6 +47,7 @@ hipError_t each_kernel(F f) {
     for (const auto *T : {&kQuarterTiles, &kPairTiles})
         for (const Tile &t : *T)
             for (const void *k : t.f) {
+                if (!k) continue;
                 hipError_t e = f(k);
                 if (e != hipSuccess) return e;
             }
@@ -59,8 +60,8 @@ bool rank2_rsplit_applies(bool pairs, int kv, int ks, int kvp, int ksp, int M, i
     return M >= 1 && pick_tile(pairs, kv, ks, kvp, ksp, M, runs) != nullptr;
 }
 
-float rank2_rsplit_us(bool pairs, int kv, int ks, int kvp, int ksp, int M, int runs) {
-    const Tile *t = M >= 1 ? pick_tile(pairs, kv, ks, kvp, ksp, M, runs) : nullptr;
+float rank2_rsplit_us(bool pairs, int kv, int ks, int kvp, int ksp, int M) {
+    const Tile *t = M >= 1 ? pick_tile(pairs, kv, ks, kvp, ksp, M, 1) : nullptr;
     return t ? t->us : INFINITY;
 }
 
@@ -74,18 +75,18 @@ hipError_t launch_rank2_rsplit(bool pairs, const void *opv, const void *ops, con
                                hipStream_t st, int mode) {
     if (r2.M < 1 || r2.nsteps < 1 || mode < kPlain || mode > kAdjoint) return hipErrorInvalidValue;
     const Tile *t = pick_tile(pairs, r2.kv, r2.ks, r2.kvp, r2.ksp, r2.M, 1);
-    if (!t) return hipErrorInvalidValue;
+    if (!t || !t->f[mode]) return hipErrorInvalidValue;
     RArgs a{}, none{};
     const hipError_t e = fill(a, t, opv, ops, r2, ws, status, st);
     return e == hipSuccess ? launch(t->f[mode], a, none, st) : e;
 }
 
-hipError_t launch_rank2_rsplit_dual(bool pairs, const void *opv0, const void *ops0, const Rank2Args &r0, void *ws0,
+hipError_t launch_rank2_rsplit_dual(const void *opv0, const void *ops0, const Rank2Args &r0, void *ws0,
                                     const void *opv1, const void *ops1, const Rank2Args &r1, void *ws1, int *status,
                                     hipStream_t st) {
     if (r0.M < 1 || r0.nsteps < 1 || r1.nsteps < 1 || r1.M != r0.M || r1.kvp != r0.kvp || r1.ksp != r0.ksp)
         return hipErrorInvalidValue;
-    const Tile *t = pick_tile(pairs, r0.kv, r0.ks, r0.kvp, r0.ksp, r0.M, 2);
+    const Tile *t = pick_tile(false, r0.kv, r0.ks, r0.kvp, r0.ksp, r0.M, 2);
     if (!t) return hipErrorInvalidValue;
     RArgs a0{}, a1{};
     hipError_t e = fill(a0, t, opv0, ops0, r0, ws0, status, st);

@@ -465,18 +465,19 @@ void rank2_rsplit_kernel(RArgs a0, RArgs a1) {
 struct Tile {
     int nch, nrb, ncb;
     float us;
-    const void *f[4];          // by Mode
+    const void *f[4];          // by Mode (kPairs: plain and traced runs only)
 };
-#define ROM_RT(P, C, B, N, US)                                                                                      \
-    {C, B, N, US, {(const void *)rank2_rsplit_kernel<P, C, B, N, kPlain>,                                               \
-               (const void *)rank2_rsplit_kernel<P, C, B, N, kTraced>,                                              \
-               (const void *)rank2_rsplit_kernel<P, C, B, N, kAdjoint>,                                             \
-               (const void *)rank2_rsplit_kernel<P, C, B, N, kDual>}}
+#define ROM_RK(P, C, B, N, MODE) (const void *)rank2_rsplit_kernel<P, C, B, N, MODE>
+#define ROM_RT_kQuarters(C, B, N, US)                                                                               \
+    {C, B, N, US, {ROM_RK(kQuarters, C, B, N, kPlain), ROM_RK(kQuarters, C, B, N, kTraced),                         \
+                   ROM_RK(kQuarters, C, B, N, kAdjoint), ROM_RK(kQuarters, C, B, N, kDual)}}
+#define ROM_RT_kPairs(C, B, N, US)                                                                                  \
+    {C, B, N, US, {ROM_RK(kPairs, C, B, N, kPlain), ROM_RK(kPairs, C, B, N, kTraced), nullptr, nullptr}}
 #define ROM_RTILES(P)                                                                                               \
-    {ROM_RT(P, 1, 1, 1, 2.4f), ROM_RT(P, 1, 2, 1, 3.3f), ROM_RT(P, 1, 2, 2, 4.0f), ROM_RT(P, 1, 4, 1, 6.5f),        \
-     ROM_RT(P, 1, 4, 2, 6.6f), ROM_RT(P, 2, 1, 1, 3.7f), ROM_RT(P, 2, 2, 1, 6.2f), ROM_RT(P, 2, 1, 2, 6.2f),        \
-     ROM_RT(P, 2, 2, 2, 10.4f), ROM_RT(P, 2, 4, 1, 10.4f), ROM_RT(P, 3, 2, 1, 8.0f), ROM_RT(P, 3, 2, 2, 15.4f),     \
-     ROM_RT(P, 4, 2, 1, 9.0f), ROM_RT(P, 4, 2, 2, 21.2f)}
+    {ROM_RT_##P(1, 1, 1, 2.4f), ROM_RT_##P(1, 2, 1, 3.3f), ROM_RT_##P(1, 2, 2, 4.0f), ROM_RT_##P(1, 4, 1, 6.5f),    \
+     ROM_RT_##P(1, 4, 2, 6.6f), ROM_RT_##P(2, 1, 1, 3.7f), ROM_RT_##P(2, 2, 1, 6.2f), ROM_RT_##P(2, 1, 2, 6.2f),    \
+     ROM_RT_##P(2, 2, 2, 10.4f), ROM_RT_##P(2, 4, 1, 10.4f), ROM_RT_##P(3, 2, 1, 8.0f), ROM_RT_##P(3, 2, 2, 15.4f), \
+     ROM_RT_##P(4, 2, 1, 9.0f), ROM_RT_##P(4, 2, 2, 21.2f)}
 constexpr int kTiles = 14;
 extern const Tile kQuarterTiles[kTiles], kPairTiles[kTiles];
 

@@ -391,7 +391,7 @@ bool rsplit_columns(rom_ctx *ctx, int M, hipStream_t st) {
         return false;
     const float cols = chains(ctx, M) ? rom::rank2_chains_us(ctx->kvp, ctx->ksp, M)
                                       : rom::rank2_f32_mfma_us(ctx->kvp, ctx->ksp);
-    return rom::rank2_rsplit_us(true, ctx->kv, ctx->ks, ctx->kvp, ctx->ksp, M, 1) < cols && !stream_capturing(st) &&
+    return rom::rank2_rsplit_us(true, ctx->kv, ctx->ks, ctx->kvp, ctx->ksp, M) < cols && !stream_capturing(st) &&
            take_sp_ws(ctx, rom::rank2_rsplit_ws_bytes(ctx->kvp, ctx->ksp, M), st) == ROM_OK;
 }
 
@@ -1338,21 +1338,13 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
     // each segment (beside the next segment's launch, which needs every CU,
     // each would wait for the other's workgroups: 437 us per segment of 31
     // steps at K = 512, M = 256, one after the other 420).
-    // Column-block sweeps (also behind an operator-resident forward sweep)
-    // that the resident row-split kernels can run take
-    // that path too up to Kv_pad = 256, where the probe, whose trace is the
-    // reverse sweep's amplitude, is summed in the same order as well, and
-    // where two of them side by side gain enough on column blocks, which have
-    // the products beside them (K = 256, us per step of the adjoint: M = 64
-    // 10.0 on column blocks, 8.9 on these; M = 256 9.7 and 11.0).
-    const bool pairs = !rev && ctx->kvp <= 256 && fsched != ROM_SCHEDULE_ROWSPLIT && fsched != ROM_SCHEDULE_PANEL &&
-                       rom::rank2_rsplit_us(true, kv, ks, ctx->kvp, ctx->ksp, M, 2) <
-                           0.6f * rom::rank2_f32_mfma_us(ctx->kvp, ctx->ksp) &&
-                       rsplit_columns(ctx, M, st);
-    const bool split_adj = (fsched == ROM_SCHEDULE_ROWSPLIT && !rev) || pairs;
-    if (pairs) ctx->kernels |= ROM_KERNEL_ROWS;
-    const size_t sp_need = pairs ? rom::rank2_rsplit_ws_bytes(ctx->kvp, ctx->ksp, M)
-                                 : rom::rank2_split_workspace_bytes(ctx->kvp, fG);
+    // Otherwise both stay on the column blocks, also where the row-split
+    // kernels that compute their sums would fit: those take turns with the
+    // products, the column blocks run beside them, and a segment is too short
+    // for the difference (K = 256, us per step of the adjoint: M = 64 9.3 on
+    // column blocks, 8.8 there, M = 256 9.7 and 11.0).
+    const bool split_adj = fsched == ROM_SCHEDULE_ROWSPLIT && !rev;
+    const size_t sp_need = rom::rank2_split_workspace_bytes(ctx->kvp, fG);
     if (split_adj && !ctx->asvT_sp) {
         const size_t pk = sizeof(float) * (size_t)ctx->kvp * ctx->ksp;
         e = hipMalloc(&ctx->asvT_sp, pk);
@@ -1465,15 +1457,14 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
     // reverse sweep and segment g - 1's recompute share a launch (disjoint
     // workgroups, a second workspace); otherwise they run one after the
     // other.
-    const bool rdual = rom::rank2_rsplit_applies(pairs, kv, ks, ctx->kvp, ctx->ksp, M, 2);
-    bool dual = split_adj && nseg > 1 && (rdual || (!pairs && rom::rank2_split_dual_width(ctx->kvp, M) >= 0));
+    const bool rdual = rom::rank2_rsplit_applies(false, kv, ks, ctx->kvp, ctx->ksp, M, 2);
+    bool dual = split_adj && nseg > 1 && (rdual || rom::rank2_split_dual_width(ctx->kvp, M) >= 0);
     // one sweep (mode 1 traced, 2 adjoint), or both side by side
     auto sweep = [&](const void *ov, const void *os, const rom::Rank2Args &r, int mode) {
-        return pairs ? rom::launch_rank2_rsplit(true, ov, os, r, ctx->sp_ws, ctx->status, st, mode)
-                     : rom::launch_rank2_split(ov, os, r, 1.0f, ctx->sp_ws, fG, ctx->status, true, st, mode);
+        return rom::launch_rank2_split(ov, os, r, 1.0f, ctx->sp_ws, fG, ctx->status, true, st, mode);
     };
     auto both = [&](const rom::Rank2Args &fw, const rom::Rank2Args &bw) {
-        return rdual ? rom::launch_rank2_rsplit_dual(pairs, ctx->avs_sp, ctx->asv_sp, fw, ctx->sp_ws, ctx->asvT_sp,
+        return rdual ? rom::launch_rank2_rsplit_dual(ctx->avs_sp, ctx->asv_sp, fw, ctx->sp_ws, ctx->asvT_sp,
                                                      ctx->avsT_sp, bw, ctx->sp_ws2, ctx->status, st)
                      : rom::launch_rank2_split_dual(ctx->avs_sp, ctx->asv_sp, fw, ctx->sp_ws, ctx->asvT_sp,
                                                     ctx->avsT_sp, bw, ctx->sp_ws2, fG, ctx->status, st);

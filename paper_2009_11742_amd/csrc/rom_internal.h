@@ -265,16 +265,16 @@ hipError_t rank2_split_f32_configure();
 // 1024: the sums of the row-split schedule, or with `pairs` those of the
 // column blocks, bit for bit.  opv, ops: split packs of Avs (kvp x ksp) and
 // Asv; ws: rank2_rsplit_ws_bytes.  mode 0: plain run; 1: traced (a.vtr, a.str
-// or null, with a.c and a.y); 2: adjoint (as launch_rank2_split).  Dual: r0
-// traced and r1 adjoint side by side.  `runs`: whether that many fit in one
-// launch.  Cooperative; not for graph capture.
+// or null, with a.c and a.y); 2, not with `pairs`: adjoint (as
+// launch_rank2_split).  Dual: r0 traced and r1 adjoint side by side, not with
+// `pairs`.  `runs`: whether that many fit in one launch.  Cooperative; not for graph capture.
 bool rank2_rsplit_applies(bool pairs, int kv, int ks, int kvp, int ksp, int M, int runs);
 // Its step in us, as measured for the tile it takes; infinity if none fits.
-float rank2_rsplit_us(bool pairs, int kv, int ks, int kvp, int ksp, int M, int runs);
+float rank2_rsplit_us(bool pairs, int kv, int ks, int kvp, int ksp, int M);
 size_t rank2_rsplit_ws_bytes(int kvp, int ksp, int M);
 hipError_t launch_rank2_rsplit(bool pairs, const void *opv, const void *ops, const Rank2Args &a, void *ws, int *status,
                                hipStream_t st, int mode);
-hipError_t launch_rank2_rsplit_dual(bool pairs, const void *opv0, const void *ops0, const Rank2Args &r0, void *ws0,
+hipError_t launch_rank2_rsplit_dual(const void *opv0, const void *ops0, const Rank2Args &r0, void *ws0,
                                     const void *opv1, const void *ops1, const Rank2Args &r1, void *ws1, int *status,
                                     hipStream_t st);
 bool rank2_rsplit_device_ok();

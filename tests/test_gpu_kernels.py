@@ -67,3 +67,32 @@ def test_column_block_runs(columns_table, kv, ks, M, kernel, call):
 def test_fp64_runs(kv, ks, M):
     assert _launched(kv, ks, M, "f64") == _lib.ROM_KERNEL_ROWS64
     assert _launched(kv, ks, M, "f64", schedule="columns") == _lib.ROM_KERNEL_VALU64
+
+
+@pytest.mark.parametrize("kv,ks,M,skew", [(256, 256, 20, True), (250, 250, 40, False), (256, 500, 30, False)])
+def test_adjoint_of_column_sweeps_does_not_wait(kv, ks, M, skew):
+    """Adjoints whose forward sweep is not on the row-split schedule enqueue
+    their sweeps (column blocks) and return: here behind another run of about
+    0.1 s on the same stream."""
+    from paper_2009_11742_amd import Rom
+    inst = synth.make_instance(kv, ks, M, seed=1, skew=skew)
+    rom = Rom(inst["Avs"], inst["Asv"], inst["b"], inst["dt"], state="f32")
+    mu = torch.tensor(inst["mu"], dtype=torch.float64, device="cuda")
+    c = torch.tensor(inst["c"], dtype=torch.float32, device="cuda")
+    rom.adjoint(mu, 40, c)          # tunes the shape, allocates
+    assert rom.last_schedule != "rowsplit"
+    big = synth.make_instance(1024, 1024, 4, seed=2)
+    long = Rom(big["Avs"], big["Asv"], big["b"], big["dt"], state="f32", schedule="columns")
+    V, S = long.zeros(4)
+    bmu = torch.tensor(big["mu"], dtype=torch.float64, device="cuda")
+    long.run_rank2(bmu, V, S, 1)
+    torch.cuda.synchronize()
+    long.run_rank2(bmu, V, S, 1500)
+    out = rom.adjoint(mu, 40, c)
+    assert not torch.cuda.current_stream().query()
+    torch.cuda.synchronize()
+    assert _lib.load().rom_debug_kernels(rom.handle) & _lib.ROM_KERNEL_COLUMNS
+    again = rom.adjoint(mu, 40, c)
+    for k in out:
+        assert torch.equal(out[k], again[k])
+    rom.close(); long.close()
