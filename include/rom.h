@@ -241,8 +241,11 @@ rom_status rom_destroy(rom_ctx *ctx);
  *                          J and y too up to Kv_pad = 256, above to FP64
  *                          rounding.  These are cooperative, with an
  *                          exchange workspace of the context (without memory
- *                          for it the column blocks run) and in-kernel waits
- *                          that rom_check reports;
+ *                          for it the column blocks run) and in-kernel waits;
+ *                          samples of a wait that ran out (another stream's or
+ *                          process's kernel held CUs for about a second) are
+ *                          left as they were and done by the column blocks in
+ *                          a launch behind the run;
  *   ROM_SCHEDULE_RESIDENT  skew pairs (Asv == -Avs^T exactly, the energy-
  *                          conserving structure of Sec. 3.1) with FP32
  *                          operators and Kv, Ks <= 256: one sample per
@@ -338,17 +341,21 @@ rom_status rom_check(rom_ctx *ctx, void *stream);
  * Test hook for the failure handling above (not for production use): with
  * on != 0, every later row-split launch of this process waits at its first
  * group exchange for data that no workgroup sends, with a short poll
- * budget, so the wait runs out, ROM_E_TIMEOUT is recorded and every later
- * wait of that launch returns at once; the kernel ends normally with
- * invalid results.  on = 0 restores normal waits.  Process-wide; returns
- * ROM_OK.
+ * budget, so the wait runs out and every later wait of that launch returns
+ * at once; the kernel ends normally.  A run on ROM_SCHEDULE_ROWSPLIT then has
+ * invalid results, and ROM_E_TIMEOUT is recorded.  The runs of other
+ * schedules that take row-split kernels (FP32 column-block runs, FP64 runs)
+ * are repeated on the column blocks and valid; the FP64 ones record
+ * ROM_E_TIMEOUT all the same under this hook.  on = 0 restores normal waits.
+ * Process-wide; returns ROM_OK.
  */
 rom_status rom_debug_force_timeout(int32_t on);
 
 /*
  * Test hook: the kernels that the context's last rom_run_rank2,
- * rom_run_receivers or rom_adjoint call launched (ROM_KERNEL_* bits; other
- * kernels have no bit).  0 for NULL.
+ * rom_run_receivers or rom_adjoint call launched (ROM_KERNEL_* bits; a repeat
+ * behind a row-split run is not counted, other kernels have no bit).  0 for
+ * NULL.
  */
 #define ROM_KERNEL_COLUMNS 1u      /* FP32 column blocks */
 #define ROM_KERNEL_CHAINS 2u       /* small FP32 models */
@@ -444,8 +451,9 @@ rom_status rom_run_rank1_batch(rom_ctx *ctx, int32_t M, const double *mu, int64_
  * row-split kernels: groups of 16 samples over the workgroups of one XCD,
  * cooperative, with an operator copy and an exchange workspace of the
  * context (allocated on the first such run; without the memory for them the
- * vector-ALU column blocks run) and in-kernel waits that
- * rom_check reports.  Under graph capture, with ROM_SCHED_COLUMNS, and
+ * vector-ALU column blocks run) and in-kernel waits, samples of one that ran
+ * out being done by the vector-ALU column blocks in a launch behind the run.
+ * Under graph capture, with ROM_SCHED_COLUMNS, and
  * where the chip is not a 256-CU gfx950 they run on the vector-ALU column
  * blocks.
  * Errors: ROM_E_ARG, ROM_E_UNSUPPORTED, ROM_E_NOMEM (panel or row-split
@@ -548,8 +556,7 @@ rom_status rom_adjoint(rom_ctx *ctx, int32_t M, const double *mu, int64_t nsteps
  *            NULL
  *
  * FP32 states and operators only, on the 4-column column-block schedule or
- * the row-split kernels that compute its sums (ROM_SCHEDULE_COLUMNS8; a wait
- * of theirs that timed out is reported by rom_check).
+ * the kernels that compute its sums (ROM_SCHEDULE_COLUMNS8).
  * The run is stepped in chunks whose state traces stay in device memory
  * (up to 2 x 256 MiB of workspace, kept by the context); the seismograms and
  * statistics of a chunk are computed on an internal stream while the next

@@ -22,11 +22,19 @@
 // stores reach the shared L2.  Every poll is bounded: one that runs out
 // records ROM_E_TIMEOUT and raises the abort word, and every later poll of
 // the launch returns at once, so the kernel always ends.
+//
+// Repeatable runs.  A wait can run out although nothing is wrong: another
+// stream's or process's kernel may hold CUs that a member of the group needs.
+// A run that would not have waited on another kernel must not fail for that:
+// its workgroups write V, S and the sums only at the end, and only if all of
+// the group got there (agree); behind it the other kernel is launched with
+// the groups' words and does the work of those that did not (committed).
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include "rom.h"
+#include "rom_internal.h"
 
 namespace rom {
 namespace xch {
@@ -89,6 +97,44 @@ __device__ __forceinline__ void wait_flags(Wait &wait, const unsigned *flag, uns
 __device__ __forceinline__ void raise_flag(unsigned *flag, unsigned phase) {
     publish_fence();
     if ((threadIdx.x & 63) == 0) __hip_atomic_store(flag, phase, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
+// The end of round t (0, 1, ..) of a group: whether all its R members have
+// come this far without a wait that ran out.  `words`: the arrivals so far,
+// and the rounds that all have agreed on, which the first member that gives
+// up freezes, so that all of them and every later reader see one answer.
+// Called by whole workgroups.  (Arrivals by compare-and-exchange on one word
+// with the answer cost up to 150 us for 32 members, these about 2.)
+constexpr unsigned kGivenUp = 0x80000000u;
+__device__ __forceinline__ bool agree(unsigned *words, unsigned R, unsigned t, Wait &wait) {
+    __shared__ int sh_all;
+    const bool bad = __syncthreads_or(wait.dead) != 0;
+    if (threadIdx.x == 0) {
+        // the answer from t to `to`, unless it is there already
+        auto settle = [&](unsigned to) {
+            unsigned v = t;
+            return __hip_atomic_compare_exchange_strong(&words[1], &v, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT) ? to : v;
+        };
+        unsigned v = t;
+        if (bad)
+            v = settle(t | kGivenUp);
+        else if (__hip_atomic_fetch_add(&words[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == (t + 1u) * R)
+            v = settle(t + 1u);
+        for (long spins = 0; v == t;) {
+            v = __hip_atomic_load(&words[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (v == t && wait.give_up(spins)) v = settle(t | kGivenUp);
+        }
+        sh_all = (v & ~kGivenUp) > t;
+    }
+    __syncthreads();
+    return sh_all != 0;
+}
+
+// Whether the run that r repeats has done sample m.
+__device__ __forceinline__ bool committed(const Repeat &r, int m) {
+    const int g = m / r.nc;
+    return (r.done[2 * (g % r.slots) + 1] & ~kGivenUp) > (unsigned)(g / r.slots);
 }
 
 __device__ __forceinline__ unsigned max3u(unsigned a, unsigned b, unsigned c) {

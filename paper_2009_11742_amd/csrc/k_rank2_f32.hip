@@ -29,6 +29,7 @@
 // reduction in chunks of kChunk terms into a fresh accumulator and folds
 // every chunk into a (hi, lo) pair with an error-free two-sum; the state
 // update itself is done in double-float (hi + lo) arithmetic.
+#include "k_exchange.h"
 #include "k_tile_f32.h"
 
 namespace rom {
@@ -285,7 +286,9 @@ template <int MODE, int NS, int TR>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void rank2_f32_mfma_kernel(Rank2Args a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    run_block<MODE, NS, TR>(a, blockIdx.x * NB * NS, smem);
+    const int col0 = blockIdx.x * NB * NS;
+    if (a.rep.done && xch::committed(a.rep, col0)) return;      // (a group's columns are whole workgroups)
+    run_block<MODE, NS, TR>(a, col0, smem);
 }
 
 // Grouped forward run: workgroup i advances the column block of instance

@@ -37,6 +37,15 @@ hipError_t fill(RArgs &a, const Tile *t, const void *opv, const void *ops, const
     return split_workspace(a.s, ws, (size_t)a.s.G * nc * kp, (size_t)a.s.G * nc * a.s.R, true, st);
 }
 
+// A repeatable run (rep): its groups' words are the flags, which these kernels
+// do not use, its status words are its own, behind the slot counters.
+void repeatable(RArgs &a, const Tile *t, Repeat *rep) {
+    if (!rep) return;
+    a.s.done = a.s.flags;
+    a.s.status = reinterpret_cast<int *>(a.s.slots + 8);
+    *rep = Repeat{a.s.done, 16 * t->ncb, a.s.G};
+}
+
 hipError_t launch(const void *f, RArgs &a0, RArgs &a1, hipStream_t st) {
     void *args[] = {&a0, &a1};
     return hipLaunchCooperativeKernel(f, dim3(kXcds * kCusPerXcd), dim3(kThreads), args, kLdsR, st);
@@ -72,12 +81,13 @@ size_t rank2_rsplit_ws_bytes(int kvp, int ksp, int M) {
 }
 
 hipError_t launch_rank2_rsplit(bool pairs, const void *opv, const void *ops, const Rank2Args &r2, void *ws, int *status,
-                               hipStream_t st, int mode) {
+                               hipStream_t st, int mode, Repeat *rep) {
     if (r2.M < 1 || r2.nsteps < 1 || mode < kPlain || mode > kAdjoint) return hipErrorInvalidValue;
     const Tile *t = pick_tile(pairs, r2.kv, r2.ks, r2.kvp, r2.ksp, r2.M, 1);
     if (!t || !t->f[mode]) return hipErrorInvalidValue;
     RArgs a{}, none{};
     const hipError_t e = fill(a, t, opv, ops, r2, ws, status, st);
+    repeatable(a, t, rep);
     return e == hipSuccess ? launch(t->f[mode], a, none, st) : e;
 }
 

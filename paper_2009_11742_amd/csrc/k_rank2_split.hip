@@ -450,8 +450,9 @@ __global__ void split_pack_kernel(const unsigned char *__restrict__ src, int fp8
     }
 }
 
-// Empty n 16-byte words of exchange slots and partials, zero flags, slot
-// counters and abort word.
+// Empty n 16-byte words of exchange slots and partials, zero flags (or the
+// words of repeatable groups), the 64 words behind them (slot counters, status
+// of repeatable runs) and the abort word.
 constexpr int kFlagWords = 128 * 128;      // 128 groups of 32 row tiles x 4 waves
 __global__ void split_clear_kernel(u4 *__restrict__ x, size_t n, unsigned *__restrict__ flags, int *__restrict__ status) {
     constexpr unsigned E = xch::kEmpty;

@@ -65,6 +65,7 @@ struct Args64 {
     u64 *x;                     // [slot][kRing][KP kNC] exchange, B-fragment order
     u64 *yp;                    // [slot][kRing][R][kNC] probe partials
     unsigned *slots;            // per-XCD slot counters
+    unsigned *done;             // [slot] two words for the end of its rounds (k_exchange.h)
     int *status;
     long spin_max;
     int forced;
@@ -194,6 +195,7 @@ void rank2_split64_kernel(Args64 a) {
         return (d[0] + d[kNC * LD]) + (d[2 * kNC * LD] + d[3 * kNC * LD]);
     };
 
+    unsigned round = 0;
     for (int g = slot; g < a.G; g += a.cap) {
         const int col0 = g * kNC, fm = col0 + fj;
         const bool fok = fm < a.M;
@@ -270,6 +272,7 @@ void rank2_split64_kernel(Args64 a) {
                 if (a.y && l < kNC && col0 + l < a.M) a.y[(size_t)k * a.M + col0 + l] = y;
             }
         }
+        if (!xch::agree(a.done + 2 * slot, R, round++, wait)) return;
 #pragma unroll
         for (int e = 0; e < NT; ++e) {
             if (fok && fr + e < a.kv) a.V[(size_t)fm * a.kv + fr + e] = sv[e];
@@ -301,12 +304,16 @@ __global__ void pack64_kernel(const double *__restrict__ A, int rows, int cols, 
     }
 }
 
-// Empty exchange slots, zero slot counters and abort word.
+// Behind the probe partials: 8 slot counters, 8 words of status, the slots'
+// words.
+constexpr int kWords64 = 16 + 2 * kXcd * kCuXcd;
+
+// Empty exchange slots, zero those words and the abort word.
 __global__ void clear64_kernel(u64 *x, size_t n, unsigned *slots, int *status) {
     const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (size_t i = i0; i < n; i += (size_t)gridDim.x * blockDim.x) x[i] = xch::kEmpty64;
-    if (i0 < 8) slots[i0] = 0u;
-    if (i0 == 8) status[2] = 0;
+    if (i0 < kWords64) slots[i0] = 0u;
+    if (i0 == 0) status[2] = 0;
 }
 
 struct Kern64 {
@@ -344,7 +351,7 @@ size_t rank2_split64_ws_bytes(int kvp, int ksp) {
         const size_t m = c * xch::kRing * kNC * ((size_t)kp + kp / RT);
         if (m > n) n = m;
     }
-    return n * sizeof(u64) + 8 * sizeof(unsigned);
+    return n * sizeof(u64) + kWords64 * sizeof(unsigned);
 }
 
 hipError_t launch_split64_pack(const double *A, int rows, int cols, int kvp, int ksp, void *dst, hipStream_t st) {
@@ -373,8 +380,10 @@ hipError_t rank2_split64_configure() {
 }
 
 // opv, ops: launch_split64_pack of Avs and Asv; ws: rank2_split64_ws_bytes.
+// The run is repeatable (rep: for the launch behind it); a time-out that was
+// forced is recorded in status all the same, so that a test sees it happen.
 hipError_t launch_rank2_split64(const void *opv, const void *ops, const Rank2Args &r2, void *ws, int *status,
-                                hipStream_t st) {
+                                hipStream_t st, Repeat &rep) {
     const Kern64 *k = kern64(r2.kvp, r2.ksp);
     if (!k || r2.M < 1 || r2.nsteps < 1) return hipErrorInvalidValue;
     Args64 a{};
@@ -387,7 +396,6 @@ hipError_t launch_rank2_split64(const void *opv, const void *ops, const Rank2Arg
     a.S = static_cast<double *>(r2.S);
     a.J = r2.J;
     a.y = r2.y;
-    a.status = status;
     a.spin_max = g_forced_timeout ? 256 : xch::kSpinMax;
     a.forced = g_forced_timeout ? 1 : 0;
     a.kv = r2.kv;
@@ -407,6 +415,9 @@ hipError_t launch_rank2_split64(const void *opv, const void *ops, const Rank2Arg
     const size_t nx = (size_t)a.cap * xch::kRing * kNC * k->kp, ny = (size_t)a.cap * xch::kRing * kNC * a.R;
     a.yp = a.x + nx;
     a.slots = reinterpret_cast<unsigned *>(a.yp + ny);
+    a.status = g_forced_timeout ? status : reinterpret_cast<int *>(a.slots + 8);
+    a.done = a.slots + 16;
+    rep = Repeat{a.done, kNC, a.cap};
     hipLaunchKernelGGL(clear64_kernel, dim3(256), dim3(256), 0, st, a.x, nx + ny, a.slots, status);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -8,6 +8,7 @@
 // increasing k with fused multiply-adds.  When both operators fit in LDS next
 // to the states they are staged there once; otherwise they are read from L2.
 #include "k_common.h"
+#include "k_exchange.h"
 #include "rom_internal.h"
 
 namespace rom {
@@ -46,6 +47,7 @@ __global__ __launch_bounds__(256) void rank2_valu_kernel(Rank2Args a, int ops_in
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int col0 = blockIdx.x * NB;
+    if (a.rep.done && xch::committed(a.rep, col0)) return;      // (a group's columns are whole workgroups)
     const T *Vin = static_cast<const T *>(a.V);
     const T *Sin = static_cast<const T *>(a.S);
     const T *bv = static_cast<const T *>(a.b);

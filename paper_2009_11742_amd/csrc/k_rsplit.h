@@ -431,6 +431,7 @@ __device__ __forceinline__ void run_rsplit(const RArgs &ra, int g, int r, unsign
         ps.load(yp, NC, rp, fs);
         probe_row(a.nsteps - 1, ps.sum(wait, yp, NC, rp, fs));
     }
+    if (a.done && !xch::agree(a.done + 2 * g, R, 0, wait)) return;
 #pragma unroll
     for (int e = 0; e < RPT; ++e) {
         const int row = fr + frow(e);

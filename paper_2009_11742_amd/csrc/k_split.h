@@ -33,6 +33,7 @@ struct SplitArgs {
     u64 *yp;                    // probe partials [group][xch::kRing][row tile][col]
     unsigned *flags;            // published phases [group][32 row tiles][wave]
     unsigned *slots;            // per-XCD slot counters (8)
+    unsigned *done;             // repeatable runs: two words per group for its end (k_exchange.h); else null
     int *status;                // status[1] <- ROM_E_TIMEOUT, status[2] abort
     float *vtr, *str;           // FP32 traced runs: state traces (entry e, sample m, row: [e][m][row])
     const double *ytr;          // adjoint runs: forward probe trace [step][m]

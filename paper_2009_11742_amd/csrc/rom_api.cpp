@@ -347,13 +347,16 @@ rom_status prepare_split64(rom_ctx *ctx, hipStream_t st) {
     return take_sp_ws(ctx, rom::rank2_split64_ws_bytes(ctx->kvp, ctx->ksp), st);
 }
 
-// FP64 row-split run; taken = false, and nothing done, without the memory
-// for its packs and workspace (the column blocks need none).
+// FP64 row-split run, its samples that a time-out left undone on the column
+// blocks behind it; taken = false, and nothing done, without the memory for
+// its packs and workspace (the column blocks need none).
 rom_status run_split64(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t st, bool &taken) {
     rom_status rs = prepare_split64(ctx, st);
     taken = rs != ROM_E_NOMEM;
     if (rs != ROM_OK) return taken ? rs : ROM_OK;
-    const hipError_t e = rom::launch_rank2_split64(ctx->avs_sp, ctx->asv_sp, a, ctx->sp_ws, ctx->status, st);
+    rom::Rank2Args again = a;
+    hipError_t e = rom::launch_rank2_split64(ctx->avs_sp, ctx->asv_sp, a, ctx->sp_ws, ctx->status, st, again.rep);
+    if (e == hipSuccess) e = rom::launch_rank2_valu<double>(again, st);
     if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
     ctx->last_schedule = -1;
     ctx->kernels |= ROM_KERNEL_ROWS64;
@@ -372,7 +375,7 @@ bool chains(const rom_ctx *ctx, int M) {
 // `launches` of them side by side.
 hipError_t launch_columns(rom_ctx *ctx, const rom::Rank2Args &a, int nset, bool adjoint, hipStream_t st,
                           int launches = 1) {
-    ctx->kernels |= chains(ctx, a.M) ? ROM_KERNEL_CHAINS : ROM_KERNEL_COLUMNS;
+    if (!a.rep.done) ctx->kernels |= chains(ctx, a.M) ? ROM_KERNEL_CHAINS : ROM_KERNEL_COLUMNS;
     if (chains(ctx, a.M)) return rom::launch_rank2_chains(a, adjoint, launches, st);
     return adjoint ? rom::launch_adjoint_f32_mfma(a, st) : rom::launch_rank2_f32_mfma(a, nset, st);
 }
@@ -383,10 +386,9 @@ hipError_t launch_columns(rom_ctx *ctx, const rom::Rank2Args &a, int nset, bool 
 // shorter (K = 256, M = 256 2.5 us against 4.6; with M = 700 groups of twice
 // the rows and columns take 5.9), unless the context pins the column blocks
 // or the stream is being captured, and only with a workspace: without the
-// memory for one the column blocks run.  (Forced time-outs are the row-split
-// schedule's.)
+// memory for one the column blocks run.
 bool rsplit_columns(rom_ctx *ctx, int M, hipStream_t st) {
-    if (!ctx->avs_sp || rom::g_forced_timeout || ctx->op_type != ROM_F32 || ctx->state_type != ROM_F32 ||
+    if (!ctx->avs_sp || ctx->op_type != ROM_F32 || ctx->state_type != ROM_F32 ||
         (ctx->flags & (ROM_SCHED_COLUMNS | ROM_SCHED_COLUMNS8)) || std::max(ctx->kvp, ctx->ksp) <= 192)
         return false;
     const float cols = chains(ctx, M) ? rom::rank2_chains_us(ctx->kvp, ctx->ksp, M)
@@ -395,10 +397,14 @@ bool rsplit_columns(rom_ctx *ctx, int M, hipStream_t st) {
            take_sp_ws(ctx, rom::rank2_rsplit_ws_bytes(ctx->kvp, ctx->ksp, M), st) == ROM_OK;
 }
 
-// The column blocks' run on the resident row-split kernels (rsplit_columns).
-rom_status run_rsplit_columns(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t st) {
-    const hipError_t e = rom::launch_rank2_rsplit(true, ctx->avs_sp, ctx->asv_sp, a, ctx->sp_ws, ctx->status, st,
-                                                   a.vtr ? 1 : 0);
+// The column blocks' run on the resident row-split kernels (rsplit_columns);
+// `again`: its arguments on the column blocks (nset column sets), which do
+// behind it what a time-out left undone (otherwise a look at one word per
+// group).
+rom_status run_rsplit_columns(rom_ctx *ctx, const rom::Rank2Args &a, rom::Rank2Args again, int nset, hipStream_t st) {
+    hipError_t e = rom::launch_rank2_rsplit(true, ctx->avs_sp, ctx->asv_sp, a, ctx->sp_ws, ctx->status, st,
+                                            a.vtr ? 1 : 0, &again.rep);
+    if (e == hipSuccess) e = launch_columns(ctx, again, nset, false, st);
     if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
     ctx->kernels |= ROM_KERNEL_ROWS;
     return sp_done(ctx, st);
@@ -408,6 +414,7 @@ rom_status run_rsplit_columns(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t
 rom_status launch_fp32_state_run(rom_ctx *ctx, rom::Rank2Args a, int sched, int G, hipStream_t st, bool timing = false) {
     hipError_t e;
     const bool lowp = ctx->op_type == ROM_BF16 || ctx->op_type == ROM_F8E4M3;
+    const int nset = sched == ROM_SCHEDULE_COLUMNS8 ? 2 : 1;
     a.single = (lowp && (ctx->flags & ROM_STATE_BF16)) ? 1 : 0;
     if (sched == ROM_SCHEDULE_PANEL) {
         return run_panel(ctx, a, st);
@@ -421,13 +428,14 @@ rom_status launch_fp32_state_run(rom_ctx *ctx, rom::Rank2Args a, int sched, int 
                                     ctx->status, !lowp, st);
         if (e == hipSuccess) return sp_done(ctx, st);
     } else if (!timing && rsplit_columns(ctx, a.M, st)) {
-        return run_rsplit_columns(ctx, a, st);
+        rom::Rank2Args again = a;
+        again.avs = ctx->avs_pk; again.asv = ctx->asv_pk;
+        return run_rsplit_columns(ctx, a, again, nset, st);
     } else if (lowp) {
         a.avs = ctx->avs_lp; a.asv = ctx->asv_lp;
         e = rom::launch_rank2_lowp(a, ctx->op_type, ctx->op_scale, st);
     } else {
         a.avs = ctx->avs_pk; a.asv = ctx->asv_pk;
-        const int nset = sched == ROM_SCHEDULE_COLUMNS8 ? 2 : 1;
         e = timing ? rom::launch_rank2_f32_mfma(a, nset, st) : launch_columns(ctx, a, nset, false, st);
     }
     if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
@@ -1609,8 +1617,8 @@ rom_status rom_run_receivers(rom_ctx *ctx, int32_t M, const double *mu, int64_t 
     // after the side stream has read it.
     hipStream_t s2 = ctx->side[0];
     rom::Rank2Args a;
-    const bool rsplit = rsplit_columns(ctx, M, st), blocks = !rsplit && !chains(ctx, M);
-    a.b = ctx->b; a.c = blocks ? C : nullptr; a.mu = mu; a.V = V; a.S = S; a.J = nullptr;
+    const bool rsplit = rsplit_columns(ctx, M, st), blocks = !chains(ctx, M);
+    a.b = ctx->b; a.c = nullptr; a.y = nullptr; a.mu = mu; a.V = V; a.S = S; a.J = nullptr;
     a.kv = kv; a.ks = ks; a.kvp = ctx->kvp; a.ksp = ctx->ksp; a.M = M; a.dt = ctx->dt; a.source = ctx_source(ctx);
     a.avs = ctx->avs_pk; a.asv = ctx->asv_pk;
     const int64_t nchunk = (nsteps + L - 1) / L;
@@ -1621,13 +1629,17 @@ rom_status rom_run_receivers(rom_ctx *ctx, int32_t M, const double *mu, int64_t 
             e = hipStreamWaitEvent(st, ctx->rc_ev[2 + b], 0);
             if (e != hipSuccess) return hip_fail(e, "rom_run_receivers: event");
         }
-        a.n0 = n0 + c * L; a.nsteps = len; a.vtr = vtr[b]; a.str = blocks ? str[b] : nullptr; a.y = blocks ? ysc[b] : nullptr;
+        a.n0 = n0 + c * L; a.nsteps = len; a.vtr = vtr[b];
+        rom::Rank2Args cb = a;
+        if (blocks) {
+            cb.c = C; cb.str = str[b]; cb.y = ysc[b];
+        }
         if (rsplit) {
-            rom_status rs = run_rsplit_columns(ctx, a, st);
+            rom_status rs = run_rsplit_columns(ctx, a, cb, 1, st);
             if (rs != ROM_OK) return rs;
             e = hipSuccess;
         } else {
-            e = launch_columns(ctx, a, 1, false, st);
+            e = launch_columns(ctx, cb, 1, false, st);
         }
         if (e == hipSuccess) e = hipEventRecord(ctx->rc_ev[b], st);
         if (e == hipSuccess) e = hipStreamWaitEvent(s2, ctx->rc_ev[b], 0);

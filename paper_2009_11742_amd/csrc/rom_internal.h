@@ -115,6 +115,14 @@ struct rom_ctx {
 
 namespace rom {
 
+// What a launch that repeats a row-split run needs to know of it: group g of
+// nc samples was round g / slots of slot g % slots, whose two words tell the
+// rounds done (k_exchange.h).  done null: not a repeat.
+struct Repeat {
+    const unsigned *done = nullptr;
+    int nc = 1, slots = 1;
+};
+
 struct Rank2Args {
     const void *avs;      // packed (F32 MFMA) or column-major (VALU path)
     const void *asv;
@@ -142,6 +150,9 @@ struct Rank2Args {
     // BF16 / FP8 operators: 1 = the state enters the products as bf16(x)
     // alone (one MFMA pass), 0 = as the BF16 pair (x_hi, x_lo)
     int single = 0;
+    // column blocks and small models: samples that an earlier run has done
+    // are left alone
+    Repeat rep;
 };
 
 // Operator-resident kernel (skew pairs, FP32): whether padded sizes fit it,
@@ -183,7 +194,7 @@ size_t rank2_split64_op_bytes(int kvp, int ksp);
 size_t rank2_split64_ws_bytes(int kvp, int ksp);
 hipError_t launch_split64_pack(const double *A, int rows, int cols, int kvp, int ksp, void *dst, hipStream_t st);
 hipError_t launch_rank2_split64(const void *opv, const void *ops, const Rank2Args &a, void *ws, int *status,
-                                hipStream_t st);
+                                hipStream_t st, Repeat &rep);
 // Whether the current device is the 256-CU gfx950 with cooperative launches
 // that the row-split kernels count on.
 bool split_chip_ok();
@@ -267,13 +278,17 @@ hipError_t rank2_split_f32_configure();
 // Asv; ws: rank2_rsplit_ws_bytes.  mode 0: plain run; 1: traced (a.vtr, a.str
 // or null, with a.c and a.y); 2, not with `pairs`: adjoint (as
 // launch_rank2_split).  Dual: r0 traced and r1 adjoint side by side, not with
-// `pairs`.  `runs`: whether that many fit in one launch.  Cooperative; not for graph capture.
+// `pairs`.  `runs`: whether that many fit in one launch.  Cooperative; not for
+// graph capture.  With rep, a run whose waits ran out has written no V, S or
+// sums (its traces are undefined), records no time-out, and is repeated by a
+// launch of other kernels with *rep behind it; without, it records
+// ROM_E_TIMEOUT in status and its results are invalid.
 bool rank2_rsplit_applies(bool pairs, int kv, int ks, int kvp, int ksp, int M, int runs);
 // Its step in us, as measured for the tile it takes; infinity if none fits.
 float rank2_rsplit_us(bool pairs, int kv, int ks, int kvp, int ksp, int M);
 size_t rank2_rsplit_ws_bytes(int kvp, int ksp, int M);
 hipError_t launch_rank2_rsplit(bool pairs, const void *opv, const void *ops, const Rank2Args &a, void *ws, int *status,
-                               hipStream_t st, int mode);
+                               hipStream_t st, int mode, Repeat *rep = nullptr);
 hipError_t launch_rank2_rsplit_dual(const void *opv0, const void *ops0, const Rank2Args &r0, void *ws0,
                                     const void *opv1, const void *ops1, const Rank2Args &r1, void *ws1, int *status,
                                     hipStream_t st);

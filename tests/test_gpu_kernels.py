@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
 def columns_table():
     """The autotuner's table with `columns` for a shape."""
     from paper_2009_11742_amd import tuning
+    tuning.load_default()
     saved = tuning.entries()
 
     def put(kv, ks, M):

@@ -1,0 +1,139 @@
+"""Runs that take row-split kernels without having been asked for that schedule
+(FP32 column-block runs, receivers, forward sweeps of adjoints, FP64 runs
+between the resident and the panel sizes) do not fail where a wait of those kernels runs
+out: the samples are left as they were and done by the column blocks behind.
+
+The time-out is forced from the host; the results must then be those of a
+context pinned to the column blocks, bit for bit, and (FP32) nothing may be
+reported.  rom_debug_kernels shows that the row-split kernels were launched.
+"""
+import numpy as np
+import pytest
+
+import synth
+from paper_2009_11742_amd import _lib
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def forced():
+    lib = _lib.load()
+    lib.rom_debug_force_timeout(1)
+    try:
+        yield
+    finally:
+        lib.rom_debug_force_timeout(0)
+
+
+@pytest.fixture
+def columns_table():
+    """The autotuner's table with `columns` for a shape."""
+    from paper_2009_11742_amd import tuning
+    tuning.load_default()
+    saved = tuning.entries()
+
+    def put(kv, ks, M):
+        up = lambda x: (x + 63) // 64 * 64
+        tuning.put(up(kv), up(ks), up(M), "f32", "columns", [1.0, -1, -1, -1, -1])
+    yield put
+    tuning.clear()
+    for e in saved:
+        tuning.put(e["kv_pad"], e["ks_pad"], e["m_pad"], e["op"], e["schedule"], e["us"])
+
+
+def _rom(inst, state, schedule="auto"):
+    from paper_2009_11742_amd import Rom
+    return Rom(inst["Avs"], inst["Asv"], inst["b"], inst["dt"], state=state, schedule=schedule)
+
+
+def _kernels(rom):
+    return _lib.load().rom_debug_kernels(rom.handle)
+
+
+def _inst(kv, ks, M):
+    return synth.round_to(synth.make_instance(kv, ks, M, seed=kv + 3 * ks + M, skew=False), "f32")
+
+
+def _run(rom, inst, M, N):
+    t = rom.torch_dtype
+    mu = torch.tensor(inst["mu"][:M], dtype=torch.float64, device="cuda")
+    V, S = rom.zeros(M)
+    V += 1e-3 * torch.tensor(inst["b"], dtype=t, device="cuda")
+    c = torch.tensor(inst["c"], dtype=t, device="cuda")
+    J = torch.ones(M, dtype=torch.float64, device="cuda")
+    y = torch.zeros((N, M), dtype=torch.float64, device="cuda")
+    rom.run_rank2(mu, V, S, N, n0=5, c=c, J=J, y=y)
+    return [V, S, J, y]
+
+
+@pytest.mark.parametrize("kv,ks,M", [(256, 256, 70), (300, 280, 33), (64, 512, 20), (500, 1000, 40), (700, 600, 128)])
+def test_column_runs_are_repeated(columns_table, forced, kv, ks, M):
+    inst = _inst(kv, ks, M)
+    columns_table(kv, ks, M)
+    outs = []
+    for sched in ("auto", "columns"):
+        rom = _rom(inst, "f32", sched)
+        outs.append(_run(rom, inst, M, 30))
+        rom.check()
+        assert _kernels(rom) == (_lib.ROM_KERNEL_ROWS if sched == "auto" else _lib.ROM_KERNEL_COLUMNS)
+        rom.close()
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("kv,ks,M,N", [(256, 200, 64, 40), (300, 340, 7, 30)])
+def test_receiver_runs_are_repeated(forced, kv, ks, M, N):
+    inst = _inst(kv, ks, M)
+    mu = torch.tensor(inst["mu"], dtype=torch.float64, device="cuda")
+    C = torch.tensor(np.random.default_rng(1).standard_normal((3, kv)), dtype=torch.float32, device="cuda")
+    outs = []
+    for sched in ("auto", "columns"):
+        rom = _rom(inst, "f32", sched)
+        V, S = rom.zeros(M)
+        o = rom.run_receivers(mu, V, S, N, C)
+        rom.check()
+        assert _kernels(rom) == (_lib.ROM_KERNEL_ROWS if sched == "auto" else _lib.ROM_KERNEL_COLUMNS)
+        outs.append([V, S, o["Y"], o["stats"]])
+        rom.close()
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+
+
+# The forward sweep (the other sweeps are on the column blocks).
+@pytest.mark.parametrize("kv,ks,M,stride", [(450, 300, 130, 0), (450, 300, 130, -1), (256, 256, 40, -1),
+                                            (250, 256, 40, 50)])
+def test_adjoints_are_repeated(columns_table, forced, kv, ks, M, stride):
+    inst = _inst(kv, ks, M)
+    columns_table(kv, ks, M)
+    mu = torch.tensor(inst["mu"], dtype=torch.float64, device="cuda")
+    c = torch.tensor(inst["c"], dtype=torch.float32, device="cuda")
+    outs = []
+    for sched in ("auto", "columns"):
+        rom = _rom(inst, "f32", sched)
+        outs.append(rom.adjoint(mu, 50, c, stride=stride))
+        rom.check()
+        assert bool(_kernels(rom) & _lib.ROM_KERNEL_ROWS) == (sched == "auto")
+        rom.close()
+    for k in outs[0]:
+        assert torch.equal(outs[0][k], outs[1][k]), k
+
+
+@pytest.mark.parametrize("kv,ks,M", [(160, 130, 20), (300, 280, 128), (192, 192, 1100)])
+def test_fp64_runs_are_repeated(forced, kv, ks, M):
+    inst = synth.make_instance(kv, ks, M, seed=kv + M, skew=False)
+    rom = _rom(inst, "f64")
+    a = _run(rom, inst, M, 12)
+    assert _kernels(rom) == _lib.ROM_KERNEL_ROWS64
+    with pytest.raises(_lib.RomError) as ei:      # (recorded because it was forced)
+        rom.check()
+    assert ei.value.status == _lib.ROM_E_TIMEOUT
+    rom.check()
+    pinned = _rom(inst, "f64", "columns")
+    b = _run(pinned, inst, M, 12)
+    assert _kernels(pinned) == _lib.ROM_KERNEL_VALU64
+    rom.close(); pinned.close()
+    for x, y in zip(a, b):
+        assert torch.equal(x, y)
