@@ -315,7 +315,8 @@ size_t rank2_f32_mfma_lds_bytes(int kvp, int ksp, int nset) {
     return state_lds_bytes(kvp, ksp, NB * nset);
 }
 
-// A step of the column blocks in us where the chip holds all of them: the
+// A step of the column blocks in us where the chip holds all of them at once
+// (4 samples each, 1024; no row-split tile that is faster holds more): the
 // wave with the most 64-row tiles runs through all its terms one after the
 // other, 8.3 ns each (measured 3.3 at K = 192, 4.6 at 256, 11 at 320, 17 at
 // 512, 67 at 1024, 5.9 at (64, 512)).

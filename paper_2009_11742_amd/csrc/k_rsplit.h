@@ -462,7 +462,8 @@ void rank2_rsplit_kernel(RArgs a0, RArgs a1) {
 
 // Tiles (NCH, NRB, NCB).  NCH = 3, 4 take 32 rows (16 rows would need more
 // than 32 workgroups per group, 64 more registers).
-// us: a step of the largest K of the class with a probe, measured.
+// us: a step of the largest K of the class with a probe, measured on kPairs
+// (kQuarters, which folds its chains in registers, takes 0.2 to 1 less).
 struct Tile {
     int nch, nrb, ncb;
     float us;
@@ -475,10 +476,10 @@ struct Tile {
 #define ROM_RT_kPairs(C, B, N, US)                                                                                  \
     {C, B, N, US, {ROM_RK(kPairs, C, B, N, kPlain), ROM_RK(kPairs, C, B, N, kTraced), nullptr, nullptr}}
 #define ROM_RTILES(P)                                                                                               \
-    {ROM_RT_##P(1, 1, 1, 2.4f), ROM_RT_##P(1, 2, 1, 3.3f), ROM_RT_##P(1, 2, 2, 4.0f), ROM_RT_##P(1, 4, 1, 6.5f),    \
-     ROM_RT_##P(1, 4, 2, 6.6f), ROM_RT_##P(2, 1, 1, 3.7f), ROM_RT_##P(2, 2, 1, 6.2f), ROM_RT_##P(2, 1, 2, 6.2f),    \
-     ROM_RT_##P(2, 2, 2, 10.4f), ROM_RT_##P(2, 4, 1, 10.4f), ROM_RT_##P(3, 2, 1, 8.0f), ROM_RT_##P(3, 2, 2, 15.4f), \
-     ROM_RT_##P(4, 2, 1, 9.0f), ROM_RT_##P(4, 2, 2, 21.2f)}
+    {ROM_RT_##P(1, 1, 1, 2.6f), ROM_RT_##P(1, 2, 1, 3.6f), ROM_RT_##P(1, 2, 2, 6.0f), ROM_RT_##P(1, 4, 1, 6.5f),    \
+     ROM_RT_##P(1, 4, 2, 9.0f), ROM_RT_##P(2, 1, 1, 3.9f), ROM_RT_##P(2, 2, 1, 5.8f), ROM_RT_##P(2, 1, 2, 6.2f),    \
+     ROM_RT_##P(2, 2, 2, 10.3f), ROM_RT_##P(2, 4, 1, 10.4f), ROM_RT_##P(3, 2, 1, 8.0f), ROM_RT_##P(3, 2, 2, 15.2f), \
+     ROM_RT_##P(4, 2, 1, 10.4f), ROM_RT_##P(4, 2, 2, 21.2f)}
 constexpr int kTiles = 14;
 extern const Tile kQuarterTiles[kTiles], kPairTiles[kTiles];
 

@@ -380,20 +380,27 @@ hipError_t launch_columns(rom_ctx *ctx, const rom::Rank2Args &a, int nset, bool 
     return adjoint ? rom::launch_adjoint_f32_mfma(a, st) : rom::launch_rank2_f32_mfma(a, nset, st);
 }
 
-// Whether a column-block run of M samples takes the resident row-split
-// kernels, which compute the same sums: FP32 operators, above 192 padded rows
-// (up to there the small models' kernels are faster than any tile), where all groups fit on the chip at once and their measured step is
-// shorter (K = 256, M = 256 2.5 us against 4.6; with M = 700 groups of twice
-// the rows and columns take 5.9), unless the context pins the column blocks
-// or the stream is being captured, and only with a workspace: without the
-// memory for one the column blocks run.
-bool rsplit_columns(rom_ctx *ctx, int M, hipStream_t st) {
+// Whether the resident row-split kernels, which compute the same sums, step a
+// column-block run of M samples faster than the column blocks or the small
+// models' kernels: FP32 operators, above 192 padded rows (up to there the
+// small models' kernels are faster than any tile), where all groups fit on the
+// chip at once and their measured step is shorter (K = 256 with a probe, M =
+// 256 2.6 us against 4.5, M = 512 3.6; above, groups of twice the columns take
+// 6.0), unless the context pins the column blocks.
+bool rsplit_faster(const rom_ctx *ctx, int M) {
     if (!ctx->avs_sp || ctx->op_type != ROM_F32 || ctx->state_type != ROM_F32 ||
         (ctx->flags & (ROM_SCHED_COLUMNS | ROM_SCHED_COLUMNS8)) || std::max(ctx->kvp, ctx->ksp) <= 192)
         return false;
     const float cols = chains(ctx, M) ? rom::rank2_chains_us(ctx->kvp, ctx->ksp, M)
                                       : rom::rank2_f32_mfma_us(ctx->kvp, ctx->ksp);
-    return rom::rank2_rsplit_us(true, ctx->kv, ctx->ks, ctx->kvp, ctx->ksp, M) < cols && !stream_capturing(st) &&
+    return rom::rank2_rsplit_us(true, ctx->kv, ctx->ks, ctx->kvp, ctx->ksp, M) < cols;
+}
+
+// Whether a column-block run takes them: where they are faster, unless the
+// stream is being captured, and only with a workspace: without the memory for
+// one the column blocks run.
+bool rsplit_columns(rom_ctx *ctx, int M, hipStream_t st) {
+    return rsplit_faster(ctx, M) && !stream_capturing(st) &&
            take_sp_ws(ctx, rom::rank2_rsplit_ws_bytes(ctx->kvp, ctx->ksp, M), st) == ROM_OK;
 }
 
@@ -551,12 +558,15 @@ int fastest(const float (&us)[ROM_NSCHEDULES], unsigned cands = ~0u) {
 }
 
 // Below 320 padded rows the tuner does not choose the row-split schedule for
-// FP32 operators: the column blocks' runs take the same resident row-split
-// kernels there (rsplit_columns), so nothing is to be gained by its other
-// summation order (K = 256, M = 64: 2.04 us per step that way, 1.94 row-split,
-// 4.4 on the column-block kernels that the tuner times).
-unsigned rs_small(const rom_ctx *ctx) {
-    return ctx->op_type == ROM_F32 && ctx->kvp < 320 ? 1u << ROM_SCHEDULE_ROWSPLIT : 0u;
+// FP32 operators where the column blocks' runs take other kernels than the
+// column-block ones that it times: the resident row-split kernels
+// (rsplit_faster: K = 256, M = 64 2.04 us per step that way, 1.94 row-split,
+// 4.4 timed) or the small models' (K = 128, M = 4096 3.4, 5.5 row-split, 7.8
+// timed), so that little or nothing is to be gained by its other summation
+// order.
+unsigned rs_small(const rom_ctx *ctx, int M) {
+    return ctx->op_type == ROM_F32 && ctx->kvp < 320 && (rsplit_faster(ctx, M) || chains(ctx, M))
+               ? 1u << ROM_SCHEDULE_ROWSPLIT : 0u;
 }
 
 // Schedule of an FP32-state rank-2 run (flags, table, or tuned now).
@@ -593,12 +603,12 @@ rom_status pick_schedule(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t st, 
         for (float &u : te.us) u = -1.f;
         rom_status rs = time_schedules(ctx, a, cands, G, kTuneSteps, st, te.us);
         if (rs != ROM_OK) return rs;
-        te.sched = fastest(te.us, cands & ~rs_small(ctx));
+        te.sched = fastest(te.us, cands & ~rs_small(ctx, a.M));
         tune_store(key, te);
     }
     // the table's choice where it applies to this context (a shape's entry
     // is shared by skew and non-skew pairs), else the fastest that does
-    sched = (cands >> te.sched & 1u) ? te.sched : fastest(te.us, cands & ~rs_small(ctx));
+    sched = (cands >> te.sched & 1u) ? te.sched : fastest(te.us, cands & ~rs_small(ctx, a.M));
     return ROM_OK;
 }
 

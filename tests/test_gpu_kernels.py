@@ -48,19 +48,44 @@ def _launched(kv, ks, M, state, schedule="auto", call="run"):
 CHAINS = [(1, 1, 1), (64, 63, 257), (113, 128, 1001), (192, 128, 40), (131, 190, 300), (256, 64, 260), (70, 193, 300),
           # 192 padded rows: no row-split tile is faster
           (192, 130, 1), (130, 192, 17), (192, 192, 700)]
-ROWS = [(256, 192, 20), (192, 256, 300), (256, 200, 128), (250, 256, 500), (256, 256, 700), (300, 280, 33),
+ROWS = [(256, 192, 20), (192, 256, 300), (256, 200, 128), (250, 256, 500), (256, 256, 512), (300, 280, 33),
         (64, 512, 16), (512, 500, 129), (512, 512, 500), (700, 600, 128), (600, 768, 250),
         (1000, 1024, 100), (1024, 900, 256)]
-BLOCKS = [(512, 40, 250)]       # no tile that holds all its groups is faster
+# No tile that holds all their groups is faster.
+BLOCKS = [(512, 40, 250), (256, 256, 513), (256, 256, 700), (200, 256, 1024), (256, 256, 1025)]
 
 
 @pytest.mark.parametrize("call", ["run", "receivers"])
 @pytest.mark.parametrize("kv,ks,M,kernel", [s + (_lib.ROM_KERNEL_CHAINS,) for s in CHAINS] +
                          [s + (_lib.ROM_KERNEL_ROWS,) for s in ROWS] + [s + (_lib.ROM_KERNEL_COLUMNS,) for s in BLOCKS])
 def test_column_block_runs(columns_table, kv, ks, M, kernel, call):
+    if call == "receivers":
+        M = min(M, 1024)        # their limit
     columns_table(kv, ks, M)
     assert _launched(kv, ks, M, "f32", call=call) == kernel
     assert _launched(kv, ks, M, "f32", schedule="columns", call=call) == _lib.ROM_KERNEL_COLUMNS
+
+
+@pytest.mark.parametrize("M", [600, 1500, 2048, 4096])
+def test_tuner_takes_the_fastest_where_columns_run_as_timed(M):
+    """K = 256: where a column-block run takes the column-block kernels, the
+    tuner may choose any schedule, row-split too."""
+    from paper_2009_11742_amd import Rom, tuning
+    tuning.load_default()
+    saved = tuning.entries()
+    inst = synth.make_instance(256, 256, M, seed=1, skew=False)
+    rom = Rom(inst["Avs"], inst["Asv"], inst["b"], inst["dt"], state="f32")
+    try:
+        tuning.clear()
+        V, S = rom.zeros(M)
+        rom.run_rank2(torch.tensor(inst["mu"], dtype=torch.float64, device="cuda"), V, S, 20)
+        times = {k: t for k, t in rom.schedule_times(M).items() if t is not None}
+        assert times[rom.last_schedule] == min(times.values()), (rom.last_schedule, times)
+    finally:
+        rom.close()
+        tuning.clear()
+        for e in saved:
+            tuning.put(e["kv_pad"], e["ks_pad"], e["m_pad"], e["op"], e["schedule"], e["us"])
 
 
 @pytest.mark.parametrize("kv,ks,M", [(128, 128, 1), (130, 70, 17), (70, 180, 16), (512, 64, 5), (64, 512, 33),
