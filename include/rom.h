@@ -236,7 +236,8 @@ rom_status rom_destroy(rom_ctx *ctx);
  *                          32-term chains run side by side; bitwise equal,
  *                          J and y included.  max(Kv_pad, Ks_pad) in [256,
  *                          1024], not captured, all samples on the chip at
- *                          once and that faster: row-split kernels that keep
+ *                          once and enough steps (K = 256: 17) for that to be
+ *                          faster: row-split kernels that keep
  *                          the operators in registers; states bitwise equal,
  *                          J and y too up to Kv_pad = 256, above to FP64
  *                          rounding.  These are cooperative, with an

@@ -386,21 +386,26 @@ hipError_t launch_columns(rom_ctx *ctx, const rom::Rank2Args &a, int nset, bool 
 // small models' kernels are faster than any tile), where all groups fit on the
 // chip at once and their measured step is shorter (K = 256 with a probe, M =
 // 256 2.6 us against 4.5, M = 512 3.6; above, groups of twice the columns take
-// 6.0), unless the context pins the column blocks.
-bool rsplit_faster(const rom_ctx *ctx, int M) {
+// 6.0), unless the context pins the column blocks.  In us per step, 0 if not.
+float rsplit_gain(const rom_ctx *ctx, int M) {
     if (!ctx->avs_sp || ctx->op_type != ROM_F32 || ctx->state_type != ROM_F32 ||
         (ctx->flags & (ROM_SCHED_COLUMNS | ROM_SCHED_COLUMNS8)) || std::max(ctx->kvp, ctx->ksp) <= 192)
-        return false;
+        return 0.f;
     const float cols = chains(ctx, M) ? rom::rank2_chains_us(ctx->kvp, ctx->ksp, M)
                                       : rom::rank2_f32_mfma_us(ctx->kvp, ctx->ksp);
-    return rom::rank2_rsplit_us(true, ctx->kv, ctx->ks, ctx->kvp, ctx->ksp, M) < cols;
+    return std::max(0.f, cols - rom::rank2_rsplit_us(true, ctx->kv, ctx->ks, ctx->kvp, ctx->ksp, M));
 }
 
-// Whether a column-block run takes them: where they are faster, unless the
-// stream is being captured, and only with a workspace: without the memory for
-// one the column blocks run.
-bool rsplit_columns(rom_ctx *ctx, int M, hipStream_t st) {
-    return rsplit_faster(ctx, M) && !stream_capturing(st) &&
+// What a row-split run costs beside its steps more than a column-block run, in
+// us: cleared exchange slots, a cooperative launch, the launch that may repeat
+// it (K = 256, M = 64, per call of one step 38 and 11, of 16 68 and 76).
+constexpr float kRsplitCallUs = 35.f;
+
+// Whether a column-block run of nsteps steps takes them: where the steps gain
+// more than the call costs, unless the stream is being captured, and only with
+// a workspace: without the memory for one the column blocks run.
+bool rsplit_columns(rom_ctx *ctx, int M, int64_t nsteps, hipStream_t st) {
+    return rsplit_gain(ctx, M) * (float)nsteps > kRsplitCallUs && !stream_capturing(st) &&
            take_sp_ws(ctx, rom::rank2_rsplit_ws_bytes(ctx->kvp, ctx->ksp, M), st) == ROM_OK;
 }
 
@@ -434,7 +439,7 @@ rom_status launch_fp32_state_run(rom_ctx *ctx, rom::Rank2Args a, int sched, int 
         e = rom::launch_rank2_split(ctx->avs_sp, ctx->asv_sp, a, lowp ? ctx->op_scale : 1.0f, ctx->sp_ws, G,
                                     ctx->status, !lowp, st);
         if (e == hipSuccess) return sp_done(ctx, st);
-    } else if (!timing && rsplit_columns(ctx, a.M, st)) {
+    } else if (!timing && rsplit_columns(ctx, a.M, a.nsteps, st)) {
         rom::Rank2Args again = a;
         again.avs = ctx->avs_pk; again.asv = ctx->asv_pk;
         return run_rsplit_columns(ctx, a, again, nset, st);
@@ -560,12 +565,12 @@ int fastest(const float (&us)[ROM_NSCHEDULES], unsigned cands = ~0u) {
 // Below 320 padded rows the tuner does not choose the row-split schedule for
 // FP32 operators where the column blocks' runs take other kernels than the
 // column-block ones that it times: the resident row-split kernels
-// (rsplit_faster: K = 256, M = 64 2.04 us per step that way, 1.94 row-split,
+// (rsplit_gain: K = 256, M = 64 2.04 us per step that way, 1.94 row-split,
 // 4.4 timed) or the small models' (K = 128, M = 4096 3.4, 5.5 row-split, 7.8
 // timed), so that little or nothing is to be gained by its other summation
 // order.
 unsigned rs_small(const rom_ctx *ctx, int M) {
-    return ctx->op_type == ROM_F32 && ctx->kvp < 320 && (rsplit_faster(ctx, M) || chains(ctx, M))
+    return ctx->op_type == ROM_F32 && ctx->kvp < 320 && (rsplit_gain(ctx, M) > 0.f || chains(ctx, M))
                ? 1u << ROM_SCHEDULE_ROWSPLIT : 0u;
 }
 
@@ -1627,7 +1632,7 @@ rom_status rom_run_receivers(rom_ctx *ctx, int32_t M, const double *mu, int64_t 
     // after the side stream has read it.
     hipStream_t s2 = ctx->side[0];
     rom::Rank2Args a;
-    const bool rsplit = rsplit_columns(ctx, M, st), blocks = !chains(ctx, M);
+    const bool rsplit = rsplit_columns(ctx, M, std::min(L, nsteps), st), blocks = !chains(ctx, M);
     a.b = ctx->b; a.c = nullptr; a.y = nullptr; a.mu = mu; a.V = V; a.S = S; a.J = nullptr;
     a.kv = kv; a.ks = ks; a.kvp = ctx->kvp; a.ksp = ctx->ksp; a.M = M; a.dt = ctx->dt; a.source = ctx_source(ctx);
     a.avs = ctx->avs_pk; a.asv = ctx->asv_pk;

@@ -29,16 +29,16 @@ def columns_table():
         tuning.put(e["kv_pad"], e["ks_pad"], e["m_pad"], e["op"], e["schedule"], e["us"])
 
 
-def _launched(kv, ks, M, state, schedule="auto", call="run"):
+def _launched(kv, ks, M, state, schedule="auto", call="run", N=200):
     from paper_2009_11742_amd import Rom
     inst = synth.make_instance(kv, ks, M, seed=1, skew=False)
     rom = Rom(inst["Avs"], inst["Asv"], inst["b"], inst["dt"], state=state, schedule=schedule)
     mu = torch.tensor(inst["mu"], dtype=torch.float64, device="cuda")
     V, S = rom.zeros(M)
     if call == "run":
-        rom.run_rank2(mu, V, S, 60)
+        rom.run_rank2(mu, V, S, N)
     else:
-        rom.run_receivers(mu, V, S, 60, torch.ones((2, kv), dtype=torch.float32, device="cuda"))
+        rom.run_receivers(mu, V, S, N, torch.ones((2, kv), dtype=torch.float32, device="cuda"))
     rom.check()
     k = _lib.load().rom_debug_kernels(rom.handle)
     rom.close()
@@ -64,6 +64,15 @@ def test_column_block_runs(columns_table, kv, ks, M, kernel, call):
     columns_table(kv, ks, M)
     assert _launched(kv, ks, M, "f32", call=call) == kernel
     assert _launched(kv, ks, M, "f32", schedule="columns", call=call) == _lib.ROM_KERNEL_COLUMNS
+
+
+@pytest.mark.parametrize("call", ["run", "receivers"])
+@pytest.mark.parametrize("kv,ks,M,short,long", [(256, 256, 64, 8, 30), (300, 280, 100, 3, 20), (500, 1000, 100, 1, 4)])
+def test_short_runs_stay_on_the_column_blocks(columns_table, kv, ks, M, short, long, call):
+    """A row-split call costs about 30 us beside its steps."""
+    columns_table(kv, ks, M)
+    assert _launched(kv, ks, M, "f32", call=call, N=short) == _lib.ROM_KERNEL_COLUMNS
+    assert _launched(kv, ks, M, "f32", call=call, N=long) == _lib.ROM_KERNEL_ROWS
 
 
 @pytest.mark.parametrize("M", [600, 1500, 2048, 4096])
