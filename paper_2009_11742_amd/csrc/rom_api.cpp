@@ -205,15 +205,16 @@ rom_status prepare_split_pack(rom_ctx *ctx, hipStream_t st) {
 }
 
 // The row-split workspace, at least `need` bytes, for a launch on `st`: it
-// is the context's, so a run on another stream than the last one's waits for
-// that run (sp_done marks its end).
+// is the context's, so every run waits for the last one (sp_done marks its
+// end; on the same stream that is nothing).  Stream handles are not compared:
+// one of a destroyed stream may come back, and that of the per-thread default
+// stream means another stream in each thread.
 rom_status take_sp_ws(rom_ctx *ctx, size_t need, hipStream_t st) {
     hipError_t e;
     if (!ctx->sp_ev) {
         e = hipEventCreateWithFlags(&ctx->sp_ev, hipEventDisableTiming);
         if (e != hipSuccess) { ctx->sp_ev = nullptr; return hip_fail(e, "rom_run_rank2: event creation"); }
-        ctx->sp_stream = st;
-    } else if (st != ctx->sp_stream) {
+    } else {
         e = hipStreamWaitEvent(st, ctx->sp_ev, 0);
         if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: event");
     }
@@ -237,7 +238,6 @@ rom_status take_sp_ws(rom_ctx *ctx, size_t need, hipStream_t st) {
 rom_status sp_done(rom_ctx *ctx, hipStream_t st) {
     const hipError_t e = hipEventRecord(ctx->sp_ev, st);
     if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: event");
-    ctx->sp_stream = st;
     return ROM_OK;
 }
 

@@ -78,9 +78,8 @@ struct rom_ctx {
     void *sp_ws = nullptr;
     size_t sp_ws_bytes = 0;
     int sp_ok = -1;
-    // Last use of sp_ws: its stream and an event behind it, so that a run on
-    // another stream waits for it.
-    hipStream_t sp_stream = nullptr;
+    // An event behind the last use of sp_ws, so that a run on another stream
+    // waits for it.
     hipEvent_t sp_ev = nullptr;
     // Operator-resident schedule (skew FP32 pairs, Kv, Ks <= 256): Avs in
     // the per-thread tile order of its kernel, built by rom_create.

@@ -137,3 +137,53 @@ def test_fp64_runs_are_repeated(forced, kv, ks, M):
     rom.close(); pinned.close()
     for x, y in zip(a, b):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("state", ["f64", "f32"])
+def test_runs_on_two_threads_default_streams(columns_table, state):
+    """hipStreamPerThread is one handle for another stream in each thread: the
+    second run, which uses the context's exchange workspace too, waits for the
+    first."""
+    import ctypes as C
+    import threading
+    kv, ks, M, N = (200, 180, 40, 3000) if state == "f64" else (256, 250, 40, 4000)
+    columns_table(kv, ks, M)
+    inst = synth.make_instance(kv, ks, M, seed=3, skew=False)
+    rom = _rom(inst, state)
+    lib, handle = _lib.load(), rom.handle
+    mu = torch.tensor(inst["mu"], dtype=torch.float64, device="cuda")
+    ref = rom.zeros(M)
+    rom.run_rank2(mu, *ref, N)
+    assert _kernels(rom) == (_lib.ROM_KERNEL_ROWS64 if state == "f64" else _lib.ROM_KERNEL_ROWS)
+    outs = [rom.zeros(M) for _ in range(2)]
+    torch.cuda.synchronize()
+    errors, first, second, end = [], threading.Event(), threading.Event(), threading.Event()
+
+    def run(V, S):
+        p = lambda t: C.c_void_p(t.data_ptr())
+        errors.append(lib.rom_run_rank2(handle, M, p(mu), 0, N, p(V), p(S), None, None, None, C.c_void_p(2)))
+
+    def one():
+        run(*outs[0])
+        first.set()
+        end.wait(60)            # (its stream ends with the thread)
+
+    def two():
+        first.wait(60)
+        run(*outs[1])
+        second.set()
+        end.wait(60)
+
+    threads = [threading.Thread(target=f) for f in (one, two)]
+    for t in threads:
+        t.start()
+    second.wait(60)
+    torch.cuda.synchronize()
+    end.set()
+    for t in threads:
+        t.join()
+    rom.check()
+    assert errors == [0, 0]
+    for V, S in outs:
+        assert torch.equal(V, ref[0]) and torch.equal(S, ref[1])
+    rom.close()
