@@ -19,7 +19,7 @@
 //
 // RT = 16 where the R = KP / 16 workgroups of every group then fit on the
 // chip, else 32: the matrix-core time of a half-step is proportional to RT
-// (KP RT 16 multiply-adds at one CU's 128 per clock), the exchange is not.
+// (KP RT 16 multiply-adds at one CU's 64 per clock), the exchange is not.
 // More groups than fit are taken in rounds: a group slot steps one group of
 // samples through the whole run, then the next.
 //
@@ -27,9 +27,11 @@
 // l: term l / 16, column l % 16; D entry v of lane l: row l / 16 + 4 v,
 // column l % 16).  Wave w sums the terms [w KP/4, (w+1) KP/4); terms come in
 // groups of 8, lane l holding terms 2 (l / 16) and 2 (l / 16) + 1 of the
-// group for two consecutive instructions.  The four partials meet in LDS and
-// one thread per RT / 16 rows of a column adds them in a fixed order and
-// updates its state entries, which live in its registers.
+// group for two consecutive instructions, each in a chain of its own.  The four
+// partials meet in LDS and one thread per RT / 16 rows of a column (one of each
+// 16-row tile) adds them in a fixed order and updates its state entries, which
+// live in its registers.  The probe is summed per 16-row tile, then over those.
+// So a sample's bits do not depend on RT, hence not on its company.
 //
 // Bound: latency.  Per half-step the matrix time is 0.5 (RT = 16) or 1.1 us
 // (RT = 32) at KP = 320; the exchange (store to L2, poll, load), about
@@ -63,7 +65,7 @@ struct Args64 {
     const double *b, *c, *mu;
     double *V, *S, *J, *y;
     u64 *x;                     // [slot][kRing][KP kNC] exchange, B-fragment order
-    u64 *yp;                    // [slot][kRing][R][kNC] probe partials
+    u64 *yp;                    // [slot][kRing][KP / 16][kNC] probe partials
     unsigned *slots;            // per-XCD slot counters
     unsigned *done;             // [slot] two words for the end of its rounds (k_exchange.h)
     int *status;
@@ -79,8 +81,8 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void rank2_split64_kernel(Args64 a) {
     constexpr int KG = KP / 32;                // 8-term groups per wave
     constexpr int NT = RT / 16;                // 16-row tiles, rows per finishing thread
+    constexpr int NP = KP / 16;                // probe partials
     constexpr int LD = RT + 2;                 // LDS column stride of the partials
-    constexpr int CH = NT == 1 ? 2 : 1;        // accumulation chains per tile
     __shared__ double part[2][kW][kNC * LD];
     __shared__ double uwin[kWin * kNC];
     __shared__ int sh_code;
@@ -101,7 +103,7 @@ void rank2_split64_kernel(Args64 a) {
 
     xch::Wait wait{a.status, a.spin_max, a.forced, false};
     u64 *const xg = a.x + (size_t)slot * xch::kRing * KP * kNC;
-    u64 *const yg = a.yp + (size_t)slot * xch::kRing * R * kNC;
+    u64 *const yg = a.yp + (size_t)slot * xch::kRing * NP * kNC;
 
     // operator fragments of this wave's terms, registers for the whole run
     d2 ov[KG][NT], os[KG][NT];
@@ -114,36 +116,41 @@ void rank2_split64_kernel(Args64 a) {
             os[g][t] = a.ops[i];
         }
 
-    // finishing thread: column fj, rows NT fs .. of the tile
+    // finishing thread: column fj, rows fs, 16 + fs, .. of the tile
     const int fj = tid >> 4, fs = tid & 15;
-    const int row0 = r * RT, fr = row0 + NT * fs;
+    const int fr = r * RT + fs;
     double bb[NT], cc[NT];
 #pragma unroll
     for (int e = 0; e < NT; ++e) {
-        bb[e] = fr + e < a.kv ? a.b[fr + e] : 0.0;
-        cc[e] = (a.c != nullptr && fr + e < a.kv) ? a.c[fr + e] : 0.0;
+        bb[e] = fr + 16 * e < a.kv ? a.b[fr + 16 * e] : 0.0;
+        cc[e] = (a.c != nullptr && fr + 16 * e < a.kv) ? a.c[fr + 16 * e] : 0.0;
     }
     const bool probe = a.c != nullptr;
-    // this thread's slot in an exchange buffer: rows fr .. of column fj
+    // this thread's slots in an exchange buffer: row fr of column fj, and the
+    // rows 16 on, kTileStep words further
     const size_t xo = (size_t)((fr >> 3) * 64 + 16 * ((fr & 7) >> 1) + fj) * 2 + (fr & 1);
+    constexpr int kTileStep = 2 * 128;
 
     int64_t q = 0, ny = 0;                     // phase, probe row to publish next
     auto publish = [&](const double (&v)[NT]) {
         u64 *d = xg + (size_t)(q & 3) * KP * kNC + xo;
 #pragma unroll
-        for (int e = 0; e < NT; ++e) xch::put64(d + e, v[e]);
+        for (int e = 0; e < NT; ++e) xch::put64(d + e * kTileStep, v[e]);
         u64 *z = xg + (size_t)((q + 2) & 3) * KP * kNC + xo;   // phase q - 2
 #pragma unroll
-        for (int e = 0; e < NT; ++e) xch::clear64(z + e);
+        for (int e = 0; e < NT; ++e) xch::clear64(z + e * kTileStep);
         ++q;
     };
-    // Probe partials have a ring of their own, one entry per step: row tile 0
-    // reads entry k before it publishes the velocity of step k + 1, so
-    // whoever publishes that of step k + 2 may empty it.
-    auto publish_y = [&](double y) {
+    // Probe partials, one per 16-row tile, have a ring of their own, one entry
+    // per step: row tile 0 reads entry k before it publishes the velocity of
+    // step k + 1, so whoever publishes that of step k + 2 may empty it.
+    auto publish_y = [&](const double (&y)[NT]) {
         if (fs == 0) {
-            xch::put64(yg + ((size_t)(ny & 3) * R + r) * kNC + fj, y);
-            xch::clear64(yg + ((size_t)((ny + 2) & 3) * R + r) * kNC + fj);
+#pragma unroll
+            for (int e = 0; e < NT; ++e) {
+                xch::put64(yg + ((size_t)(ny & 3) * NP + NT * r + e) * kNC + fj, y[e]);
+                xch::clear64(yg + ((size_t)((ny + 2) & 3) * NP + NT * r + e) * kNC + fj);
+            }
         }
         ++ny;
     };
@@ -167,31 +174,27 @@ void rank2_split64_kernel(Args64 a) {
         }
         // (the emptied slots of the last publication: before the next one)
         xch::publish_fence();
-        d4 acc[NT][CH];
+        d4 acc[NT][2];
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int h = 0; h < CH; ++h) acc[t][h] = d4{0.0, 0.0, 0.0, 0.0};
+            for (int h = 0; h < 2; ++h) acc[t][h] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int g = 0; g < KG; ++g)
 #pragma unroll
             for (int e = 0; e < 2; ++e)
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
-                    acc[t][e % CH] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                        op[g][t][e], __builtin_bit_cast(double, x[g][e]), acc[t][e % CH], 0, 0, 0);
+                    acc[t][e] = __builtin_amdgcn_mfma_f64_16x16x4f64(op[g][t][e], __builtin_bit_cast(double, x[g][e]),
+                                                                     acc[t][e], 0, 0, 0);
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                double sum = acc[t][0][v];
-                if constexpr (CH == 2) sum += acc[t][1][v];
-                pw[(l & 15) * LD + 16 * t + (l >> 4) + 4 * v] = sum;
-            }
+            for (int v = 0; v < 4; ++v) pw[(l & 15) * LD + 16 * t + (l >> 4) + 4 * v] = acc[t][0][v] + acc[t][1][v];
     };
     // sum of the four waves' partials of this thread's row e
     auto total = [&](const double *p, int e) {
-        const double *d = p + fj * LD + NT * fs + e;
+        const double *d = p + fj * LD + 16 * e + fs;
         return (d[0] + d[kNC * LD]) + (d[2 * kNC * LD] + d[3 * kNC * LD]);
     };
 
@@ -202,8 +205,8 @@ void rank2_split64_kernel(Args64 a) {
         double sv[NT], ss[NT];
 #pragma unroll
         for (int e = 0; e < NT; ++e) {
-            sv[e] = (fok && fr + e < a.kv) ? a.V[(size_t)fm * a.kv + fr + e] : 0.0;
-            ss[e] = (fok && fr + e < a.ks) ? a.S[(size_t)fm * a.ks + fr + e] : 0.0;
+            sv[e] = (fok && fr + 16 * e < a.kv) ? a.V[(size_t)fm * a.kv + fr + 16 * e] : 0.0;
+            ss[e] = (fok && fr + 16 * e < a.ks) ? a.S[(size_t)fm * a.ks + fr + 16 * e] : 0.0;
         }
         xch::publish_fence();
         publish(ss);
@@ -221,18 +224,21 @@ void rank2_split64_kernel(Args64 a) {
             products(ov, &part[0][w][0]);
             __syncthreads();
             const double u = uwin[(int)(k % kWin) * kNC + fj];
-            double yt = 0.0;
+            double yt[NT];
 #pragma unroll
             for (int e = 0; e < NT; ++e) {
                 const double inc = fma(bb[e], u, total(&part[0][0][0], e));
-                sv[e] = fr + e < a.kv ? fma(a.dt, inc, sv[e]) : 0.0;
-                yt = fma(cc[e], sv[e], yt);
+                sv[e] = fr + 16 * e < a.kv ? fma(a.dt, inc, sv[e]) : 0.0;
+                yt[e] = cc[e] * sv[e];
             }
             if (probe) {                       // over the column's 16 threads (one 16-lane row)
-                yt += lane::dpp_mov64<lane::kDppRor8>(yt);
-                yt += lane::dpp_mov64<lane::kDppHalfMirror>(yt);
-                yt += lane::dpp_mov64<lane::kDppXor2>(yt);
-                yt += lane::dpp_mov64<lane::kDppXor1>(yt);
+#pragma unroll
+                for (int e = 0; e < NT; ++e) {
+                    yt[e] += lane::dpp_mov64<lane::kDppRor8>(yt[e]);
+                    yt[e] += lane::dpp_mov64<lane::kDppHalfMirror>(yt[e]);
+                    yt[e] += lane::dpp_mov64<lane::kDppXor2>(yt[e]);
+                    yt[e] += lane::dpp_mov64<lane::kDppXor1>(yt[e]);
+                }
             }
             publish(sv);
             if (probe) publish_y(yt);
@@ -241,7 +247,7 @@ void rank2_split64_kernel(Args64 a) {
             __syncthreads();
 #pragma unroll
             for (int e = 0; e < NT; ++e)
-                ss[e] = fr + e < a.ks ? fma(a.dt, total(&part[1][0][0], e), ss[e]) : 0.0;
+                ss[e] = fr + 16 * e < a.ks ? fma(a.dt, total(&part[1][0][0], e), ss[e]) : 0.0;
             // the last stress field is not read; a further group's first
             // publication takes its phase
             if (k + 1 < a.nsteps) {
@@ -250,23 +256,22 @@ void rank2_split64_kernel(Args64 a) {
             // ---- probe: row tile 0 sums the group's partials of this step,
             // in the time it would wait for the stress rows
             if (probe && r == 0 && w == 0) {
-                constexpr int NP = (KP / RT + 3) / 4;
-                const u64 *p = yg + (size_t)((ny - 1) & 3) * R * kNC + (l & 15);
-                u64 v[NP];
+                static_assert(NP % 4 == 0, "four quarters of the wave");
+                const u64 *p = yg + ((size_t)((ny - 1) & 3) * NP + (l >> 4)) * kNC + (l & 15);
+                u64 v[NP / 4];
                 long spins = 0;
                 for (;;) {
                     unsigned m = 0;
 #pragma unroll
-                    for (int i = 0; i < NP; ++i) v[i] = xch::get64(p + (size_t)min(4 * i + (l >> 4), R - 1) * kNC);
+                    for (int i = 0; i < NP / 4; ++i) v[i] = xch::get64(p + (size_t)4 * i * kNC);
 #pragma unroll
-                    for (int i = 0; i < NP; ++i) m = xch::max3u(m, m, (unsigned)(v[i] >> 32));
+                    for (int i = 0; i < NP / 4; ++i) m = xch::max3u(m, m, (unsigned)(v[i] >> 32));
                     if (wait.dead || __ballot(m == xch::kEmpty) == 0) break;
                     if (wait.give_up(spins)) break;
                 }
                 double y = 0.0;
 #pragma unroll
-                for (int i = 0; i < NP; ++i)
-                    if (4 * i + (l >> 4) < R) y += __builtin_bit_cast(double, v[i]);
+                for (int i = 0; i < NP / 4; ++i) y += __builtin_bit_cast(double, v[i]);
                 y = lane::swap_sum64<true>(lane::swap_sum64<false>(y));
                 Jacc = fma(a.dt, y * y, Jacc);
                 if (a.y && l < kNC && col0 + l < a.M) a.y[(size_t)k * a.M + col0 + l] = y;
@@ -275,8 +280,8 @@ void rank2_split64_kernel(Args64 a) {
         if (!xch::agree(a.done + 2 * slot, R, round++, wait)) return;
 #pragma unroll
         for (int e = 0; e < NT; ++e) {
-            if (fok && fr + e < a.kv) a.V[(size_t)fm * a.kv + fr + e] = sv[e];
-            if (fok && fr + e < a.ks) a.S[(size_t)fm * a.ks + fr + e] = ss[e];
+            if (fok && fr + 16 * e < a.kv) a.V[(size_t)fm * a.kv + fr + 16 * e] = sv[e];
+            if (fok && fr + 16 * e < a.ks) a.S[(size_t)fm * a.ks + fr + 16 * e] = ss[e];
         }
         if (probe && a.J && r == 0 && w == 0 && l < kNC && col0 + l < a.M) a.J[col0 + l] += Jacc;
     }
@@ -348,7 +353,7 @@ size_t rank2_split64_ws_bytes(int kvp, int ksp) {
     size_t n = 0;
     for (int RT = 16; RT <= 32; RT += 16) {
         const size_t c = slots64(kp, RT);
-        const size_t m = c * xch::kRing * kNC * ((size_t)kp + kp / RT);
+        const size_t m = c * xch::kRing * kNC * ((size_t)kp + kp / 16);
         if (m > n) n = m;
     }
     return n * sizeof(u64) + kWords64 * sizeof(unsigned);
@@ -412,7 +417,7 @@ hipError_t launch_rank2_split64(const void *opv, const void *ops, const Rank2Arg
     const int cap = slots64(k->kp, RT);
     a.cap = a.G < cap ? a.G : cap;
     a.x = static_cast<u64 *>(ws);
-    const size_t nx = (size_t)a.cap * xch::kRing * kNC * k->kp, ny = (size_t)a.cap * xch::kRing * kNC * a.R;
+    const size_t nx = (size_t)a.cap * xch::kRing * kNC * k->kp, ny = (size_t)a.cap * xch::kRing * kNC * (k->kp / 16);
     a.yp = a.x + nx;
     a.slots = reinterpret_cast<unsigned *>(a.yp + ny);
     a.status = g_forced_timeout ? status : reinterpret_cast<int *>(a.slots + 8);

@@ -147,3 +147,16 @@ def test_split64_captured_run_stays_on_the_column_blocks():
         rom.run_rank2(mu, *rom.zeros(6), 5)
         torch.cuda.synchronize()
     rom.close(); pinned.close()
+
+
+@pytest.mark.parametrize("kv,ks,M,few", [(192, 150, 900, [899, 4, 640]), (128, 128, 600, list(range(250, 290))),
+                                         (300, 280, 390, [0, 17, 389]), (64, 512, 140, [139]), (512, 64, 140, [3, 70])])
+def test_split64_bits_do_not_depend_on_the_company(kv, ks, M, few):
+    """More samples than 16-row tiles hold at once (32-row tiles, (192, 150)
+    and (300, 280) in rounds) against some of them alone (16-row tiles)."""
+    inst = synth.make_instance(kv, ks, M, seed=kv + M, skew=False)
+    rom = _rom(inst)
+    big, alone = _run(rom, inst, inst["mu"], 40, n0=2), _run(rom, inst, inst["mu"][few], 40, n0=2)
+    rom.close()
+    for a, b in zip((big[0][few], big[1][few], big[2][few], big[3][:, few]), alone):
+        assert np.array_equal(a, b)
