@@ -454,6 +454,8 @@ rom_status rom_run_rank1_batch(rom_ctx *ctx, int32_t M, const double *mu, int64_
  * context (allocated on the first such run; without the memory for them the
  * vector-ALU column blocks run) and in-kernel waits, samples of one that ran
  * out being done by the vector-ALU column blocks in a launch behind the run.
+ * Runs of up to 4 steps of a few hundred samples take ordinary launches, one
+ * per half-step, with the same sums.
  * Under graph capture, with ROM_SCHED_COLUMNS, and
  * where the chip is not a 256-CU gfx950 they run on the vector-ALU column
  * blocks.

@@ -59,6 +59,7 @@ constexpr int kWin = 16;           // steps of forcing evaluated at a time
 constexpr int kXcd = 8, kCuXcd = 32;
 // one workgroup per CU, so that each XCD takes 32 of the 256
 constexpr size_t kLds64 = 96 * 1024;
+constexpr int kShort64 = 4;        // see rank2_split64_short
 
 struct Args64 {
     const d2 *opv, *ops;        // packed fragments (see pack64_kernel)
@@ -86,13 +87,58 @@ __device__ __forceinline__ KernArgs64 &args_here() {
     return *p;
 }
 
+constexpr int ld64(int NT) { return 16 * NT + 2; }     // LDS column stride of the partials
+
+// A wave's partials of its NT 16-row tiles, to LDS: the first and the second
+// terms of its KG groups in a chain each.
+template <int KG, int NT>
+__device__ __forceinline__ void partials64(const d2 (&op)[KG][NT], const u64 (&x)[KG][2], int l, double *pw) {
+    d4 acc[NT][2];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) acc[t][h] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int g = 0; g < KG; ++g)
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                acc[t][e] = __builtin_amdgcn_mfma_f64_16x16x4f64(op[g][t][e], __builtin_bit_cast(double, x[g][e]),
+                                                                 acc[t][e], 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            pw[(l & 15) * ld64(NT) + 16 * t + (l >> 4) + 4 * v] = acc[t][0][v] + acc[t][1][v];
+}
+
+// The sum of the four waves' partials of one row.
+template <int NT>
+__device__ __forceinline__ double total64(const double *d) {
+    constexpr int W = kNC * ld64(NT);
+    return (d[0] + d[W]) + (d[2 * W] + d[3 * W]);
+}
+
+// The sum over a column's 16 threads (one 16-lane row).
+__device__ __forceinline__ double tile_sum64(double y) {
+    y += lane::dpp_mov64<lane::kDppRor8>(y);
+    y += lane::dpp_mov64<lane::kDppHalfMirror>(y);
+    y += lane::dpp_mov64<lane::kDppXor2>(y);
+    y += lane::dpp_mov64<lane::kDppXor1>(y);
+    return y;
+}
+
+// The sum over the four 16-lane rows.
+__device__ __forceinline__ double rows_sum64(double y) { return lane::swap_sum64<true>(lane::swap_sum64<false>(y)); }
+
 template <int KP, int RT>
 __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void rank2_split64_kernel(Args64 a) {
     constexpr int KG = KP / 32;                // 8-term groups per wave
     constexpr int NT = RT / 16;                // 16-row tiles, rows per finishing thread
     constexpr int NP = KP / 16;                // probe partials
-    constexpr int LD = RT + 2;                 // LDS column stride of the partials
+    constexpr int LD = ld64(NT);
     __shared__ double part[2][kW][kNC * LD];
     __shared__ double uwin[kWin * kNC];
     __shared__ int sh_code;
@@ -184,28 +230,11 @@ void rank2_split64_kernel(Args64 a) {
         }
         // (the emptied slots of the last publication: before the next one)
         xch::publish_fence();
-        d4 acc[NT][2];
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) acc[t][h] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int g = 0; g < KG; ++g)
-#pragma unroll
-            for (int e = 0; e < 2; ++e)
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    acc[t][e] = __builtin_amdgcn_mfma_f64_16x16x4f64(op[g][t][e], __builtin_bit_cast(double, x[g][e]),
-                                                                     acc[t][e], 0, 0, 0);
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) pw[(l & 15) * LD + 16 * t + (l >> 4) + 4 * v] = acc[t][0][v] + acc[t][1][v];
+        partials64<KG, NT>(op, x, l, pw);
     };
     // sum of the four waves' partials of this thread's row e
     auto total = [&](const double *p, int e) {
-        const double *d = p + fj * LD + 16 * e + fs;
-        return (d[0] + d[kNC * LD]) + (d[2 * kNC * LD] + d[3 * kNC * LD]);
+        return total64<NT>(p + fj * LD + 16 * e + fs);
     };
 
     unsigned round = 0;
@@ -242,14 +271,9 @@ void rank2_split64_kernel(Args64 a) {
                 sv[e] = fr + 16 * e < a.kv ? fma(a.dt, inc, sv[e]) : 0.0;
                 yt[e] = cc[e] * sv[e];
             }
-            if (probe) {                       // over the column's 16 threads (one 16-lane row)
+            if (probe) {
 #pragma unroll
-                for (int e = 0; e < NT; ++e) {
-                    yt[e] += lane::dpp_mov64<lane::kDppRor8>(yt[e]);
-                    yt[e] += lane::dpp_mov64<lane::kDppHalfMirror>(yt[e]);
-                    yt[e] += lane::dpp_mov64<lane::kDppXor2>(yt[e]);
-                    yt[e] += lane::dpp_mov64<lane::kDppXor1>(yt[e]);
-                }
+                for (int e = 0; e < NT; ++e) yt[e] = tile_sum64(yt[e]);
             }
             publish(sv);
             if (probe) publish_y(yt);
@@ -283,7 +307,7 @@ void rank2_split64_kernel(Args64 a) {
                 double y = 0.0;
 #pragma unroll
                 for (int i = 0; i < NP / 4; ++i) y += __builtin_bit_cast(double, v[i]);
-                y = lane::swap_sum64<true>(lane::swap_sum64<false>(y));
+                y = rows_sum64(y);
                 Jacc = fma(a.dt, y * y, Jacc);
                 if (a.y && l < kNC && col0 + l < a.M) a.y[(size_t)k * a.M + col0 + l] = y;
             }
@@ -297,6 +321,72 @@ void rank2_split64_kernel(Args64 a) {
         }
         if (probe && out.J && r == 0 && w == 0 && l < kNC && col0 + l < out.M) out.J[col0 + l] += Jacc;
     }
+}
+
+// Runs of a few steps: a launch per half-step, which needs no exchange, no
+// cooperative launch and no cleared slots (about 30 us per call), with the
+// sums of the kernel above, so that a run cut into single steps gives the same
+// bits.  Workgroup R g + r: rows 16 r .. of the field for group g, the other
+// field's terms read from the caller's states.  Bound by its launches, 5 us a
+// step at the small sizes.  Measured, us per call of one step, vector-ALU
+// blocks / row-split kernel / here: (128, 128), M = 3 18 / 36 / 12, (160, 160),
+// M = 64 27 / 38 / 11, (300, 280), M = 128 86 / 42 / 11.
+struct Half64 {
+    const d2 *op;
+    const double *x;            // the other field's states, n entries a column
+    double *f;                  // this field's, rows entries a column
+    const double *b, *c, *mu;   // velocity half-step: source, probe (or null); b null in the other
+    double *yp;                 // probe partials [group][16-row tile][kNC]
+    int n, rows, M, source;
+    double t, dt;
+};
+
+template <int KP>
+__global__ __launch_bounds__(kT) void rank2_half64_kernel(Half64 a) {
+    constexpr int KG = KP / 32, R = KP / 16;
+    __shared__ double part[kW][kNC * ld64(1)];
+    const int tid = threadIdx.x, l = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = blockIdx.x % R, g = blockIdx.x / R, col0 = g * kNC;
+    d2 op[KG][1];
+    u64 x[KG][2];
+    const int m = col0 + (l & 15);
+#pragma unroll
+    for (int q = 0; q < KG; ++q) {
+        op[q][0] = a.op[((size_t)(r * kW + w) * KG + q) * 64 + l];
+        const int k = w * (KP / 4) + 8 * q + 2 * (l >> 4);
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+            x[q][e] = __builtin_bit_cast(u64, m < a.M && k + e < a.n ? a.x[(size_t)m * a.n + k + e] : 0.0);
+    }
+    partials64<KG, 1>(op, x, l, part[w]);
+    __syncthreads();
+    const int fj = tid >> 4, fs = tid & 15, row = 16 * r + fs, fm = col0 + fj;
+    const bool ok = fm < a.M && row < a.rows;
+    double inc = total64<1>(&part[0][fj * ld64(1) + fs]), v = ok ? a.f[(size_t)fm * a.rows + row] : 0.0;
+    if (a.b)
+        inc = fma(row < a.rows ? a.b[row] : 0.0, fm < a.M ? dev::forcing(a.source, a.t, a.mu[fm]) : 0.0, inc);
+    v = row < a.rows ? fma(a.dt, inc, v) : 0.0;
+    if (ok) a.f[(size_t)fm * a.rows + row] = v;
+    if (a.c) {
+        const double y = tile_sum64((row < a.rows ? a.c[row] : 0.0) * v);
+        if (fs == 0) a.yp[((size_t)g * R + r) * kNC + fj] = y;
+    }
+}
+
+// The probe of such a run, a wave per group: yp [step][group][R][kNC].
+__global__ __launch_bounds__(64) void rank2_half64_probe_kernel(const double *yp, int nsteps, int R, int M, double dt,
+                                                                double *J, double *y) {
+    const int l = threadIdx.x, g = blockIdx.x, m = g * kNC + l;
+    double Jacc = 0.0;
+    for (int k = 0; k < nsteps; ++k) {
+        const double *p = yp + (((size_t)k * gridDim.x + g) * R + (l >> 4)) * kNC + (l & 15);
+        double v = 0.0;
+        for (int i = 0; i < R / 4; ++i) v += p[(size_t)4 * i * kNC];
+        v = rows_sum64(v);
+        Jacc = fma(dt, v * v, Jacc);
+        if (y && l < kNC && m < M) y[(size_t)k * M + m] = v;
+    }
+    if (J && l < kNC && m < M) J[m] += Jacc;
 }
 
 // Fragments of a column-major rows x cols operator zero padded to KP x KP:
@@ -336,8 +426,11 @@ __global__ void clear64_kernel(u64 *x, size_t n, unsigned *slots, int *status) {
 struct Kern64 {
     int kp;
     const void *f[2];          // RT = 16, 32
+    const void *half;
 };
-#define ROM_K64(KP) {KP, {(const void *)rank2_split64_kernel<KP, 16>, (const void *)rank2_split64_kernel<KP, 32>}}
+#define ROM_K64(KP)                                                                                     \
+    {KP, {(const void *)rank2_split64_kernel<KP, 16>, (const void *)rank2_split64_kernel<KP, 32>},      \
+     (const void *)rank2_half64_kernel<KP>}
 const Kern64 kKern64[] = {ROM_K64(128), ROM_K64(192), ROM_K64(256), ROM_K64(320),
                           ROM_K64(384), ROM_K64(448), ROM_K64(512)};
 #undef ROM_K64
@@ -440,6 +533,50 @@ hipError_t launch_rank2_split64(const void *opv, const void *ops, const Rank2Arg
     if (e != hipSuccess) return e;
     void *args[] = {&a};
     return hipLaunchCooperativeKernel(k->f[ri], dim3(kXcd * kCuXcd), dim3(kT), args, kLds64, st);
+}
+
+// Steps up to which a launch per half-step is faster than one cooperative
+// launch at every size, and samples up to which its workgroups, of 16 rows,
+// fill the chip about twice (four steps: (128, 128), M = 3 26 us against 43,
+// (64, 512), M = 33 43 against 59, (192, 192), M = 500 49 against 52).
+bool rank2_split64_short(int kvp, int ksp, int M, int64_t nsteps) {
+    const Kern64 *k = kern64(kvp, ksp);
+    return k && nsteps <= kShort64 && (M + kNC - 1) / kNC <= slots64(k->kp, 32);
+}
+
+// Such a run; ws (rank2_split64_ws_bytes) only for a probe.
+hipError_t launch_rank2_short64(const void *opv, const void *ops, const Rank2Args &r2, void *ws, hipStream_t st) {
+    const Kern64 *k = kern64(r2.kvp, r2.ksp);
+    if (!rank2_split64_short(r2.kvp, r2.ksp, r2.M, r2.nsteps) || r2.M < 1 || (r2.c && !ws)) return hipErrorInvalidValue;
+    const int R = k->kp / 16, G = (r2.M + kNC - 1) / kNC;
+    Half64 v{}, s{};
+    v.op = static_cast<const d2 *>(opv);
+    s.op = static_cast<const d2 *>(ops);
+    v.f = static_cast<double *>(r2.V);
+    s.f = static_cast<double *>(r2.S);
+    v.x = s.f;
+    s.x = v.f;
+    v.rows = s.n = r2.kv;
+    v.n = s.rows = r2.ks;
+    v.b = static_cast<const double *>(r2.b);
+    v.c = static_cast<const double *>(r2.c);
+    v.mu = r2.mu;
+    v.M = s.M = r2.M;
+    v.dt = s.dt = r2.dt;
+    v.source = r2.source;
+    for (int64_t i = 0; i < r2.nsteps; ++i) {
+        v.t = (double)(r2.n0 + i) * r2.dt;
+        v.yp = static_cast<double *>(ws) + (size_t)i * G * R * kNC;
+        for (Half64 *h : {&v, &s}) {
+            void *args[] = {h};
+            const hipError_t e = hipLaunchKernel(k->half, dim3(R * G), dim3(kT), args, 0, st);
+            if (e != hipSuccess) return e;
+        }
+    }
+    if (r2.c && (r2.J || r2.y))
+        hipLaunchKernelGGL(rank2_half64_probe_kernel, dim3(G), dim3(64), 0, st, static_cast<const double *>(ws),
+                           (int)r2.nsteps, R, r2.M, r2.dt, r2.J, r2.y);
+    return hipGetLastError();
 }
 
 }  // namespace rom

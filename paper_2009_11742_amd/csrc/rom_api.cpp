@@ -324,8 +324,9 @@ bool split64_candidate(rom_ctx *ctx, hipStream_t st) {
     return split_device(ctx);
 }
 
-// Operator packs and workspace of an FP64 row-split run, built on first use.
-rom_status prepare_split64(rom_ctx *ctx, hipStream_t st) {
+// Operator packs and, with `work`, the workspace of an FP64 row-split run,
+// built on first use.
+rom_status prepare_split64(rom_ctx *ctx, bool work, hipStream_t st) {
     if (!ctx->avs_sp) {
         const size_t ob = rom::rank2_split64_op_bytes(ctx->kvp, ctx->ksp);
         hipError_t e = hipMalloc(&ctx->avs_sp, ob);
@@ -344,22 +345,28 @@ rom_status prepare_split64(rom_ctx *ctx, hipStream_t st) {
                                             : hip_fail(e, "rom_run_rank2: row-split setup");
         }
     }
-    return take_sp_ws(ctx, rom::rank2_split64_ws_bytes(ctx->kvp, ctx->ksp), st);
+    return work ? take_sp_ws(ctx, rom::rank2_split64_ws_bytes(ctx->kvp, ctx->ksp), st) : ROM_OK;
 }
 
 // FP64 row-split run, its samples that a time-out left undone on the column
 // blocks behind it; taken = false, and nothing done, without the memory for
 // its packs and workspace (the column blocks need none).
 rom_status run_split64(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t st, bool &taken) {
-    rom_status rs = prepare_split64(ctx, st);
+    const bool few = rom::rank2_split64_short(ctx->kvp, ctx->ksp, a.M, a.nsteps), work = !few || a.c;
+    rom_status rs = prepare_split64(ctx, work, st);
     taken = rs != ROM_E_NOMEM;
     if (rs != ROM_OK) return taken ? rs : ROM_OK;
+    ctx->last_schedule = -1;
+    ctx->kernels |= ROM_KERNEL_ROWS64;
+    if (few) {
+        const hipError_t e = rom::launch_rank2_short64(ctx->avs_sp, ctx->asv_sp, a, work ? ctx->sp_ws : nullptr, st);
+        if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
+        return work ? sp_done(ctx, st) : ROM_OK;
+    }
     rom::Rank2Args again = a;
     hipError_t e = rom::launch_rank2_split64(ctx->avs_sp, ctx->asv_sp, a, ctx->sp_ws, ctx->status, st, again.rep);
     if (e == hipSuccess) e = rom::launch_rank2_valu<double>(again, st);
     if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
-    ctx->last_schedule = -1;
-    ctx->kernels |= ROM_KERNEL_ROWS64;
     return sp_done(ctx, st);
 }
 

@@ -194,6 +194,10 @@ size_t rank2_split64_ws_bytes(int kvp, int ksp);
 hipError_t launch_split64_pack(const double *A, int rows, int cols, int kvp, int ksp, void *dst, hipStream_t st);
 hipError_t launch_rank2_split64(const void *opv, const void *ops, const Rank2Args &a, void *ws, int *status,
                                 hipStream_t st, Repeat &rep);
+// The same, bit for bit, for runs of a few steps, in ordinary launches (ws
+// only with a probe).
+bool rank2_split64_short(int kvp, int ksp, int M, int64_t nsteps);
+hipError_t launch_rank2_short64(const void *opv, const void *ops, const Rank2Args &a, void *ws, hipStream_t st);
 // Whether the current device is the 256-CU gfx950 with cooperative launches
 // that the row-split kernels count on.
 bool split_chip_ok();

@@ -160,3 +160,27 @@ def test_split64_bits_do_not_depend_on_the_company(kv, ks, M, few):
     rom.close()
     for a, b in zip((big[0][few], big[1][few], big[2][few], big[3][:, few]), alone):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("kv,ks,M", [(128, 128, 3), (130, 70, 17), (300, 280, 40), (64, 512, 33), (512, 64, 5)])
+@pytest.mark.parametrize("cut", [1, 2, 4])
+def test_split64_run_cut_into_few_steps(kv, ks, M, cut):
+    """Runs of a few steps, launched per half-step, give the states and the
+    probe trace of one run, bit for bit; J to the order of its sum."""
+    inst = synth.make_instance(kv, ks, M, seed=kv + M, skew=False)
+    rom = _rom(inst)
+    N = 12
+    V, S, J, y = _run(rom, inst, inst["mu"], N, n0=4)
+    mu = torch.tensor(inst["mu"], dtype=torch.float64, device="cuda")
+    c = torch.tensor(inst["c"], dtype=torch.float64, device="cuda")
+    (V2, S2), (V3, S3) = rom.zeros(M), rom.zeros(M)
+    J2 = torch.zeros(M, dtype=torch.float64, device="cuda")
+    y2 = torch.zeros((N, M), dtype=torch.float64, device="cuda")
+    for k in range(0, N, cut):
+        rom.run_rank2(mu, V2, S2, cut, n0=4 + k, c=c, J=J2, y=y2[k:k + cut])
+        rom.run_rank2(mu, V3, S3, cut, n0=4 + k)
+    rom.check()
+    rom.close()
+    for a, b in ((V, V2), (S, S2), (y, y2), (V, V3), (S, S3)):
+        assert np.array_equal(a, b.cpu().numpy())
+    assert np.max(np.abs(J2.cpu().numpy() - J) / J) <= 1e-14
