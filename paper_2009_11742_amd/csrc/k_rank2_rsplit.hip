@@ -13,8 +13,9 @@ using namespace rsplit;
 // equals).
 const Tile *pick_tile(bool pairs, int kv, int ks, int kvp, int ksp, int M, int runs) {
     const int kp = kvp > ksp ? kvp : ksp, k = kv > ks ? kv : ks, nch = (kp + 255) / 256;
-    const Tile *best = nullptr;
-    for (const Tile &t : pairs ? kPairTiles : kQuarterTiles) {
+    const Tile *best = nullptr, *tiles = pairs ? kPairTiles : kQuarterTiles;
+    for (int i = 0; i < (pairs ? kPairCount : kQuarterCount); ++i) {
+        const Tile &t = tiles[i];
         if (t.nch != nch) continue;
         const int R = (k + 16 * t.nrb - 1) / (16 * t.nrb), G = (M + 16 * t.ncb - 1) / (16 * t.ncb);
         if (R > kCusPerXcd || runs * G > kXcds * (kCusPerXcd / R)) continue;
@@ -53,14 +54,14 @@ hipError_t launch(const void *f, RArgs &a0, RArgs &a1, hipStream_t st) {
 
 template <class F>
 hipError_t each_kernel(F f) {
-    for (const auto *T : {&kQuarterTiles, &kPairTiles})
-        for (const Tile &t : *T)
-            for (const void *k : t.f) {
-                if (!k) continue;
-                hipError_t e = f(k);
-                if (e != hipSuccess) return e;
-            }
-    return hipSuccess;
+    hipError_t e = hipSuccess;
+    auto tile = [&](const Tile &t) {
+        for (const void *k : t.f)
+            if (k && e == hipSuccess) e = f(k);
+    };
+    for (const Tile &t : kQuarterTiles) tile(t);
+    for (const Tile &t : kPairTiles) tile(t);
+    return e;
 }
 
 }  // namespace

@@ -22,11 +22,11 @@
 // width gives bitwise the same states; only the probe's FP64 row sum is
 // associated differently.
 //
-// Operator rows: where a wave has at most two chains per field (K <= 512)
-// and the group is narrow they stay in registers for the run (64 per chain
-// and field); else they are streamed from L2 every half-step.  Plain runs of
-// narrow groups up to K = 1024 take the smaller row tiles of
-// k_rank2_rsplit.hip instead, bitwise the same.
+// Operator rows: where a wave has two chains per field (K = 320 .. 512) and the
+// group 32 columns they stay in registers for the run (64 per chain and field);
+// else they are streamed from L2 every half-step.  Up to K = 1024 and the
+// samples that its groups hold, k_rank2_rsplit.hip with smaller row tiles runs
+// instead, bitwise the same.
 #include <type_traits>
 
 #include "k_lane.h"
@@ -68,7 +68,7 @@ __device__ __forceinline__ u4 ld_shared(gbyte *p) {
 // Streamed products of one field for wave w: acc[rb][cb][r] = sum over the
 // wave's KG k-groups of op rows 16 rb .. x state columns 16 cb ..
 // KGT: k-groups per wave (K / 64) when fixed at compile time (fully
-// unrolled; K = 256, 512, 1024), 0 for any K that is a multiple of 64 (KG
+// unrolled; K = 1024 with 32 columns), 0 for any K that is a multiple of 64 (KG
 // taken at run time).  Both forms issue the same MFMAs in the same order
 // (FP32 chains of 4 k-groups, the last one shorter when KG % 4 != 0, each
 // folded into FP64 at its end), so they give the same sums.  The group's
@@ -591,49 +591,49 @@ __global__ void split_pack_f32_kernel(const float *__restrict__ A, int rows, int
     }
 }
 
-// Kernels by kind and width, [kind index][width index]: streamed, resident
-// with 1 and 2 chains per wave.  Plain and traced runs take these only where
-// k_rank2_rsplit.hip has no tile (more samples than its groups hold, K >
-// 1024), where one chain per wave never occurs with 16 or 32 columns, nor
-// two with 16; the compile-time k-group count pays at K = 1024 with 32
-// columns.
-const void *const kF32Plain[3][3] = {
-    {(const void *)rank2_split_f32_kernel<0, false, 1>, (const void *)rank2_split_f32_kernel<0, false, 2>,
-     (const void *)rank2_split_f32_kernel<0, false, 4>},
-    {nullptr, nullptr, nullptr},
-    {nullptr, (const void *)rank2_split_f32_kernel<2, false, 2>, nullptr}};
+// Streamed kernels by width index, and the resident ones, two chains per wave
+// with 32 columns.  Runs take these only where k_rank2_rsplit.hip has no tile
+// (more samples than its groups hold, K > 1024), where one chain per wave
+// never occurs with 16 or 32 columns, nor two with 16; the compile-time k-group
+// count pays at K = 1024 with 32 columns.
+struct KernelSet {
+    const void *streamed[3], *resident;
+};
+constexpr int kResidentWidth = 1;
+const KernelSet kF32Plain = {{(const void *)rank2_split_f32_kernel<0, false, 1>,
+                              (const void *)rank2_split_f32_kernel<0, false, 2>,
+                              (const void *)rank2_split_f32_kernel<0, false, 4>},
+                             (const void *)rank2_split_f32_kernel<2, false, 2>};
 const void *const kF32Plain1024 = (const void *)rank2_split_f32_kernel<-16, false, 2>;
-const void *const kF32Traced[3][3] = {{(const void *)rank2_split_f32_kernel<0, false, 1, kSplitTraced>,
-                                       (const void *)rank2_split_f32_kernel<0, false, 2, kSplitTraced>,
-                                       (const void *)rank2_split_f32_kernel<0, false, 4, kSplitTraced>}};
-const void *const kF32Adjoint[3][3] = {{(const void *)rank2_split_f32_kernel<0, false, 1, kSplitAdjoint>,
-                                        (const void *)rank2_split_f32_kernel<0, false, 2, kSplitAdjoint>,
-                                        (const void *)rank2_split_f32_kernel<0, false, 4, kSplitAdjoint>},
-                                       {(const void *)rank2_split_f32_kernel<1, false, 1, kSplitAdjoint>,
-                                        (const void *)rank2_split_f32_kernel<1, false, 2, kSplitAdjoint>, nullptr},
-                                       {(const void *)rank2_split_f32_kernel<2, false, 1, kSplitAdjoint>,
-                                        (const void *)rank2_split_f32_kernel<2, false, 2, kSplitAdjoint>, nullptr}};
+const KernelSet kF32Traced = {{(const void *)rank2_split_f32_kernel<0, false, 1, kSplitTraced>,
+                               (const void *)rank2_split_f32_kernel<0, false, 2, kSplitTraced>,
+                               (const void *)rank2_split_f32_kernel<0, false, 4, kSplitTraced>},
+                              nullptr};
+const KernelSet kF32Adjoint = {{(const void *)rank2_split_f32_kernel<0, false, 1, kSplitAdjoint>,
+                                (const void *)rank2_split_f32_kernel<0, false, 2, kSplitAdjoint>,
+                                (const void *)rank2_split_f32_kernel<0, false, 4, kSplitAdjoint>},
+                               (const void *)rank2_split_f32_kernel<2, false, 2, kSplitAdjoint>};
 const void *const kF32Grouped = (const void *)rank2_split_f32_kernel<0, true, 4>;
-const void *const kF32Dual[3][3] = {
-    {(const void *)rank2_split_f32_dual_kernel<0, 1>, (const void *)rank2_split_f32_dual_kernel<0, 2>,
-     (const void *)rank2_split_f32_dual_kernel<0, 4>},
-    {(const void *)rank2_split_f32_dual_kernel<1, 1>, (const void *)rank2_split_f32_dual_kernel<1, 2>, nullptr},
-    {(const void *)rank2_split_f32_dual_kernel<2, 1>, (const void *)rank2_split_f32_dual_kernel<2, 2>, nullptr}};
+const KernelSet kF32Dual = {{(const void *)rank2_split_f32_dual_kernel<0, 1>,
+                             (const void *)rank2_split_f32_dual_kernel<0, 2>,
+                             (const void *)rank2_split_f32_dual_kernel<0, 4>},
+                            (const void *)rank2_split_f32_dual_kernel<2, 2>};
 
-// Kind index of a kernel of table T at padded size kp and width 16 << wi.
-int kind_index(const void *const (&T)[3][3], int kp, int wi) {
-    const int nb = (kp / kRows + kCG - 1) / kCG;       // chains per wave
-    return nb <= 2 && T[nb][wi] ? nb : 0;
+// Whether the runs of a set at padded size kp and width 16 << wi have a
+// resident kernel (two chains per wave: K in 320 .. 512).
+bool resident(const KernelSet &s, int kp, int wi) {
+    return s.resident && wi == kResidentWidth && (kp / kRows + kCG - 1) / kCG == 2;
 }
 
 template <class F>
 hipError_t each_kernel(F f) {
     hipError_t e = f(kF32Grouped);
     if (e == hipSuccess) e = f(kF32Plain1024);
-    for (const auto *T : {&kF32Plain, &kF32Traced, &kF32Adjoint, &kF32Dual})
-        for (const auto &r : *T)
-            for (const void *k : r)
-                if (e == hipSuccess && k) e = f(k);
+    for (const KernelSet *s : {&kF32Plain, &kF32Traced, &kF32Adjoint, &kF32Dual}) {
+        for (const void *k : s->streamed)
+            if (e == hipSuccess) e = f(k);
+        if (e == hipSuccess && s->resident) e = f(s->resident);
+    }
     return e;
 }
 
@@ -686,12 +686,12 @@ hipError_t launch_rank2_split_f32(const void *opv, const void *ops, const Rank2A
     // sized for G 64-column groups, covers it
     const int wi = split_width_index(a.M, a.kp), nc = 16 << wi;
     a.G = (a.M + nc - 1) / nc;
-    const auto &T = mode == kSplitPlain ? kF32Plain : (mode == kSplitTraced ? kF32Traced : kF32Adjoint);
-    const int ki = kind_index(T, a.kp, wi);
-    hipError_t e = split_workspace(a, ws, (size_t)a.G * nc * a.kp, (size_t)a.G * a.R * nc, ki > 0, st);
+    const KernelSet &s = mode == kSplitPlain ? kF32Plain : (mode == kSplitTraced ? kF32Traced : kF32Adjoint);
+    const bool res = resident(s, a.kp, wi);
+    hipError_t e = split_workspace(a, ws, (size_t)a.G * nc * a.kp, (size_t)a.G * a.R * nc, res, st);
     if (e != hipSuccess) return e;
     void *args[] = {&a};
-    const void *f = mode == kSplitPlain && a.kp == 1024 && wi == 1 ? kF32Plain1024 : T[ki][wi];
+    const void *f = mode == kSplitPlain && a.kp == 1024 && wi == 1 ? kF32Plain1024 : res ? s.resident : s.streamed[wi];
     return hipLaunchCooperativeKernel(f, dim3(256), dim3(kThreads), args, kLdsF32, st);
 }
 
@@ -715,13 +715,13 @@ hipError_t launch_rank2_split_dual(const void *opv0, const void *ops0, const Ran
     a0.G = a1.G = (r0.M + nc - 1) / nc;
     if (a0.G * nc > G * kCols) return hipErrorInvalidValue;    // the workspaces hold G 64-column groups
     const size_t nx = (size_t)a0.G * nc * a0.kp, ny = (size_t)a0.G * a0.R * nc;
-    const int ki = kind_index(kF32Dual, a0.kp, wi);
-    hipError_t e = split_workspace(a0, ws0, nx, ny, ki > 0, st);
-    if (e == hipSuccess) e = split_workspace(a1, ws1, nx, ny, ki > 0, st);
+    const bool res = resident(kF32Dual, a0.kp, wi);
+    hipError_t e = split_workspace(a0, ws0, nx, ny, res, st);
+    if (e == hipSuccess) e = split_workspace(a1, ws1, nx, ny, res, st);
     if (e != hipSuccess) return e;
     void *args[] = {&a0, &a1};
-    return hipLaunchCooperativeKernel(kF32Dual[ki][wi], dim3(256), dim3(kThreads), args, kLdsF32,
-                                      st);
+    return hipLaunchCooperativeKernel(res ? kF32Dual.resident : kF32Dual.streamed[wi], dim3(256), dim3(kThreads), args,
+                                      kLdsF32, st);
 }
 
 bool rank2_split_f32_device_ok() {

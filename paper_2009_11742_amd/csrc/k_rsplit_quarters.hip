@@ -4,7 +4,9 @@
 namespace rom {
 namespace rsplit {
 
-const Tile kQuarterTiles[kTiles] = ROM_RTILES(kQuarters);
+const Tile kQuarterTiles[kQuarterCount] = {ROM_RT_kQuarters(1, 1, 1, 2.6f), ROM_RT_kQuarters(1, 2, 1, 3.6f),
+                                           ROM_RT_kQuarters(1, 2, 2, 6.0f), ROM_RT_kQuarters(1, 4, 2, 9.0f),
+                                           ROM_RT_LONG(kQuarters)};
 
 }  // namespace rsplit
 }  // namespace rom
