@@ -575,10 +575,15 @@ int fastest(const float (&us)[ROM_NSCHEDULES], unsigned cands = ~0u) {
 // (rsplit_gain: K = 256, M = 64 2.04 us per step that way, 1.94 row-split,
 // 4.4 timed) or the small models' (K = 128, M = 4096 3.4, 5.5 row-split, 7.8
 // timed), so that little or nothing is to be gained by its other summation
-// order.
+// order.  Nor for BF16 and FP8 operators at 128 padded rows, where the tuner
+// preferred the column blocks until the exchange got faster (3.3 and 3.6 us per
+// step at every M; row-split 4.1, now 3.1): so little is not worth other bits
+// in the results and waits inside the kernel.
 unsigned rs_small(const rom_ctx *ctx, int M) {
-    return ctx->op_type == ROM_F32 && ctx->kvp < 320 && (rsplit_gain(ctx, M) > 0.f || chains(ctx, M))
-               ? 1u << ROM_SCHEDULE_ROWSPLIT : 0u;
+    const bool columns = ctx->op_type == ROM_F32
+                             ? ctx->kvp < 320 && (rsplit_gain(ctx, M) > 0.f || chains(ctx, M))
+                             : ctx->kvp == 128;
+    return columns ? 1u << ROM_SCHEDULE_ROWSPLIT : 0u;
 }
 
 // Schedule of an FP32-state rank-2 run (flags, table, or tuned now).

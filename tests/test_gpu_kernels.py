@@ -131,3 +131,27 @@ def test_adjoint_of_column_sweeps_does_not_wait(kv, ks, M, skew):
     for k in out:
         assert torch.equal(out[k], again[k])
     rom.close(); long.close()
+
+
+@pytest.mark.parametrize("ops", ["bf16", "fp8"])
+@pytest.mark.parametrize("K,M", [(128, 1), (91, 142), (128, 600)])
+def test_tuner_keeps_small_low_precision_models_on_column_blocks(ops, K, M):
+    from paper_2009_11742_amd import Rom, tuning
+    tuning.load_default()
+    saved = tuning.entries()
+    inst = synth.make_instance(K, K, M, seed=1)
+    outs = []
+    try:
+        tuning.clear()
+        for schedule in ("auto", "columns"):
+            rom = Rom(inst["Avs"], inst["Asv"], inst["b"], inst["dt"], state="f32", ops=ops, schedule=schedule)
+            V, S = rom.zeros(M)
+            rom.run_rank2(torch.tensor(inst["mu"], dtype=torch.float64, device="cuda"), V, S, 30)
+            assert rom.last_schedule == "columns"
+            outs.append((V, S))
+            rom.close()
+    finally:
+        tuning.clear()
+        for e in saved:
+            tuning.put(e["kv_pad"], e["ks_pad"], e["m_pad"], e["op"], e["schedule"], e["us"])
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
