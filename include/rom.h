@@ -49,7 +49,9 @@
  *    rom_run_receivers); a few synchronise `stream` (a rank-2 run that tunes
  *    its schedule, rom_create, rom_check, rom_run_grouped), as their
  *    comments say.
- *  - A context is not thread-safe; distinct contexts are independent.
+ *  - A context is not thread-safe; distinct contexts are independent.  Launches
+ *    whose workgroups wait for each other (row-split kernels) take turns on
+ *    the GPU within a process, whatever their streams.
  */
 #ifndef ROM_H
 #define ROM_H
@@ -236,17 +238,16 @@ rom_status rom_destroy(rom_ctx *ctx);
  *                          32-term chains run side by side; bitwise equal,
  *                          J and y included.  max(Kv_pad, Ks_pad) in [256,
  *                          1024], not captured, all samples on the chip at
- *                          once and enough steps (K = 256: 17) for that to be
- *                          faster: row-split kernels that keep
- *                          the operators in registers; states bitwise equal,
- *                          J and y too up to Kv_pad = 256, above to FP64
- *                          rounding.  These are cooperative, with an
- *                          exchange workspace of the context (without memory
- *                          for it the column blocks run) and in-kernel waits;
- *                          samples of a wait that ran out (another stream's or
- *                          process's kernel held CUs for about a second) are
- *                          left as they were and done by the column blocks in
- *                          a launch behind the run;
+ *                          once and enough steps (K = 256: 10) for that to be
+ *                          faster: row-split kernels that keep the operators
+ *                          in registers; states bitwise equal, J and y too up
+ *                          to Kv_pad = 256, above to FP64 rounding.  These
+ *                          have an exchange workspace of the context (without
+ *                          memory for it the column blocks run) and in-kernel
+ *                          waits; samples of a wait that ran out (another
+ *                          stream's or process's kernel held CUs for about a
+ *                          second) are left as they were and done by the
+ *                          column blocks in a launch behind the run;
  *   ROM_SCHEDULE_RESIDENT  skew pairs (Asv == -Avs^T exactly, the energy-
  *                          conserving structure of Sec. 3.1) with FP32
  *                          operators and Kv, Ks <= 256: one sample per
@@ -450,15 +451,14 @@ rom_status rom_run_rank1_batch(rom_ctx *ctx, int32_t M, const double *mu, int64_
  * FP64 states between the resident kernel's sizes and the panel schedule's
  * (Kv_pad + Ks_pad < 768, max(Kv_pad, Ks_pad) in [128, 512]) run on FP64
  * row-split kernels: groups of 16 samples over the workgroups of one XCD,
- * cooperative, with an operator copy and an exchange workspace of the
- * context (allocated on the first such run; without the memory for them the
- * vector-ALU column blocks run) and in-kernel waits, samples of one that ran
- * out being done by the vector-ALU column blocks in a launch behind the run.
- * Runs of up to 4 steps of a few hundred samples take ordinary launches, one
- * per half-step, with the same sums.
- * Under graph capture, with ROM_SCHED_COLUMNS, and
- * where the chip is not a 256-CU gfx950 they run on the vector-ALU column
- * blocks.
+ * with an operator copy and an exchange workspace of the context (allocated
+ * on the first such run; without the memory for them the vector-ALU column
+ * blocks run) and in-kernel waits, samples of one that ran out being done by
+ * the vector-ALU column blocks in a launch behind the run.  Runs of up to 3
+ * steps of a few hundred samples take one launch per half-step, with the same
+ * sums and no waits.  A sample's bits depend neither on its company nor on how
+ * a run is cut.  Under graph capture, with ROM_SCHED_COLUMNS, and where the
+ * chip is not a 256-CU gfx950 they run on the vector-ALU column blocks.
  * Errors: ROM_E_ARG, ROM_E_UNSUPPORTED, ROM_E_NOMEM (panel or row-split
  * workspace), ROM_E_DEVICE, ROM_E_TIMEOUT.
  */

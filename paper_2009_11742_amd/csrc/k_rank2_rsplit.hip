@@ -49,7 +49,7 @@ void repeatable(RArgs &a, const Tile *t, Repeat *rep) {
 
 hipError_t launch(const void *f, RArgs &a0, RArgs &a1, hipStream_t st) {
     void *args[] = {&a0, &a1};
-    return hipLaunchCooperativeKernel(f, dim3(kXcds * kCusPerXcd), dim3(kThreads), args, kLdsR, st);
+    return launch_waiting(f, args, kLdsR, st, a0.s.done == nullptr);
 }
 
 template <class F>

@@ -629,8 +629,25 @@ hipError_t launch_rank2_split(const void *opv, const void *ops, const Rank2Args 
     if (e != hipSuccess) return e;
     void *args[] = {&a};
     const int idx = a.kp / 128 - 1;   // k-blocks per wave - 1 (K a multiple of 128, checked above)
-    return hipLaunchCooperativeKernel(kSplitLpKernels[6 * idx + 3 * (r2.single ? 1 : 0) + wi], dim3(256),
-                                      dim3(kThreads), args, rank2_split_lds_bytes(), st);
+    return launch_waiting(kSplitLpKernels[6 * idx + 3 * (r2.single ? 1 : 0) + wi], args, rank2_split_lds_bytes(), st, true);
+}
+
+hipError_t launch_waiting(const void *f, void **args, size_t lds, hipStream_t st, bool together) {
+    constexpr int kMaxDevices = 64;
+    static std::mutex mu;
+    static hipEvent_t last[kMaxDevices] = {};      // behind the device's last such launch
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+    // (held until the launch is recorded: the next one, of any thread, waits
+    // for this one)
+    std::lock_guard<std::mutex> lk(mu);
+    e = last[dev] ? hipStreamWaitEvent(st, last[dev], 0) : hipEventCreateWithFlags(&last[dev], hipEventDisableTiming);
+    if (e != hipSuccess) return e;
+    const dim3 grid(kXcds * kCusPerXcd), block(kThreads);
+    e = together ? hipLaunchCooperativeKernel(f, grid, block, args, lds, st) : hipLaunchKernel(f, grid, block, args, lds, st);
+    return e == hipSuccess ? hipEventRecord(last[dev], st) : e;
 }
 
 // The schedule needs all 256 workgroups resident at once, one per CU, 32 on

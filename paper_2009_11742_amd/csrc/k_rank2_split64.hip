@@ -59,7 +59,6 @@ constexpr int kWin = 16;           // steps of forcing evaluated at a time
 constexpr int kXcd = 8, kCuXcd = 32;
 // one workgroup per CU, so that each XCD takes 32 of the 256
 constexpr size_t kLds64 = 96 * 1024;
-constexpr int kShort64 = 4;        // see rank2_split64_short
 
 struct Args64 {
     const d2 *opv, *ops;        // packed fragments (see pack64_kernel)
@@ -324,13 +323,13 @@ void rank2_split64_kernel(Args64 a) {
 }
 
 // Runs of a few steps: a launch per half-step, which needs no exchange, no
-// cooperative launch and no cleared slots (about 30 us per call), with the
-// sums of the kernel above, so that a run cut into single steps gives the same
-// bits.  Workgroup R g + r: rows 16 r .. of the field for group g, the other
-// field's terms read from the caller's states.  Bound by its launches, 5 us a
-// step at the small sizes.  Measured, us per call of one step, vector-ALU
-// blocks / row-split kernel / here: (128, 128), M = 3 18 / 36 / 12, (160, 160),
-// M = 64 27 / 38 / 11, (300, 280), M = 128 86 / 42 / 11.
+// cleared slots and no launch that may repeat it, with the sums of the kernel
+// above, so that a run cut into single steps gives the same bits.  Workgroup
+// R g + r: rows 16 r .. of the field for group g, the other field's terms read
+// from the caller's states.  Bound by its launches, 5 us a step at the small
+// sizes.  Measured, us per call of one step, vector-ALU blocks / row-split
+// kernel / here: (128, 128), M = 3 18 / 21 / 12, (192, 192), M = 500 32 / 27 / 13,
+// (300, 280), M = 128 86 / 27 / 12.
 struct Half64 {
     const d2 *op;
     const double *x;            // the other field's states, n entries a column
@@ -532,16 +531,19 @@ hipError_t launch_rank2_split64(const void *opv, const void *ops, const Rank2Arg
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     void *args[] = {&a};
-    return hipLaunchCooperativeKernel(k->f[ri], dim3(kXcd * kCuXcd), dim3(kT), args, kLds64, st);
+    static_assert(kT == 256 && kXcd * kCuXcd == 256, "launch_waiting");
+    return launch_waiting(k->f[ri], args, kLds64, st, false);
 }
 
-// Steps up to which a launch per half-step is faster than one cooperative
-// launch at every size, and samples up to which its workgroups, of 16 rows,
-// fill the chip about twice (four steps: (128, 128), M = 3 26 us against 43,
-// (64, 512), M = 33 43 against 59, (192, 192), M = 500 49 against 52).
+// Whether a launch per half-step is faster than the exchanging kernel: three
+// steps of as many samples as 16-row tiles hold at once ((128, 128), M = 3 21 us
+// against 25, (64, 512), M = 33 32 against 38, (300, 280), M = 128 26 against 34;
+// four 26, 42, 35 against 27, 43, 38), two of as many as 32-row tiles hold
+// ((192, 192), M = 500 25 against 31, three 37 against 34).
 bool rank2_split64_short(int kvp, int ksp, int M, int64_t nsteps) {
     const Kern64 *k = kern64(kvp, ksp);
-    return k && nsteps <= kShort64 && (M + kNC - 1) / kNC <= slots64(k->kp, 32);
+    const int G = (M + kNC - 1) / kNC;
+    return k && G <= slots64(k->kp, 32) && nsteps <= (G <= slots64(k->kp, 16) ? 3 : 2);
 }
 
 // Such a run; ws (rank2_split64_ws_bytes) only for a probe.

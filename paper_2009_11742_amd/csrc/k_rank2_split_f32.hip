@@ -670,7 +670,7 @@ hipError_t launch_grouped_split_f32(const SplitGroup *grp_dev, int g0, int G, co
     hipError_t e = split_workspace(a, ws, xfloats, 0, false, st);
     if (e != hipSuccess) return e;
     void *args[] = {&a};
-    return hipLaunchCooperativeKernel(kF32Grouped, dim3(256), dim3(kThreads), args, kLdsF32, st);
+    return launch_waiting(kF32Grouped, args, kLdsF32, st, true);
 }
 
 // mode: kSplitPlain, kSplitTraced, kSplitAdjoint.
@@ -692,7 +692,7 @@ hipError_t launch_rank2_split_f32(const void *opv, const void *ops, const Rank2A
     if (e != hipSuccess) return e;
     void *args[] = {&a};
     const void *f = mode == kSplitPlain && a.kp == 1024 && wi == 1 ? kF32Plain1024 : res ? s.resident : s.streamed[wi];
-    return hipLaunchCooperativeKernel(f, dim3(256), dim3(kThreads), args, kLdsF32, st);
+    return launch_waiting(f, args, kLdsF32, st, true);
 }
 
 int rank2_split_dual_width(int kvp, int M) {
@@ -720,8 +720,7 @@ hipError_t launch_rank2_split_dual(const void *opv0, const void *ops0, const Ran
     if (e == hipSuccess) e = split_workspace(a1, ws1, nx, ny, res, st);
     if (e != hipSuccess) return e;
     void *args[] = {&a0, &a1};
-    return hipLaunchCooperativeKernel(res ? kF32Dual.resident : kF32Dual.streamed[wi], dim3(256), dim3(kThreads), args,
-                                      kLdsF32, st);
+    return launch_waiting(res ? kF32Dual.resident : kF32Dual.streamed[wi], args, kLdsF32, st, true);
 }
 
 bool rank2_split_f32_device_ok() {

@@ -404,9 +404,9 @@ float rsplit_gain(const rom_ctx *ctx, int M) {
 }
 
 // What a row-split run costs beside its steps more than a column-block run, in
-// us: cleared exchange slots, a cooperative launch, the launch that may repeat
-// it (K = 256, M = 64, per call of one step 38 and 11, of 16 68 and 76).
-constexpr float kRsplitCallUs = 35.f;
+// us: cleared exchange slots, the launch that may repeat it (K = 256, M = 64,
+// per call of 8 steps 37 and 42, of none 21 and 7).
+constexpr float kRsplitCallUs = 18.f;
 
 // Whether a column-block run of nsteps steps takes them: where the steps gain
 // more than the call costs, unless the stream is being captured, and only with

@@ -183,8 +183,8 @@ bool rank2_resident64_applies(int kvp, int ksp, bool skew);
 hipError_t launch_rank2_resident64(const Rank2Args &a, bool skew, hipStream_t st);
 
 // FP64 states: the row-split schedule between the resident and the panel
-// kernels' sizes (max(Kv_pad, Ks_pad) in 128 .. 512; a 256-CU gfx950;
-// cooperative launch, not for graph capture).  opv / ops: packs of Avs and
+// kernels' sizes (max(Kv_pad, Ks_pad) in 128 .. 512; a 256-CU gfx950; not for
+// graph capture).  opv / ops: packs of Avs and
 // Asv, rank2_split64_op_bytes each; ws: rank2_split64_ws_bytes.
 bool rank2_split64_applies(int kvp, int ksp);
 bool rank2_split64_device_ok();
@@ -198,6 +198,14 @@ hipError_t launch_rank2_split64(const void *opv, const void *ops, const Rank2Arg
 // only with a probe).
 bool rank2_split64_short(int kvp, int ksp, int M, int64_t nsteps);
 hipError_t launch_rank2_short64(const void *opv, const void *ops, const Rank2Args &a, void *ws, hipStream_t st);
+// A launch of 256 workgroups of 256 threads that wait for each other (and
+// fill the chip, one per CU), behind the last one of the process on this
+// device, whatever its stream: two of them at once could each hold CUs that
+// the other needs.  `together`: cooperative, for runs that cannot be repeated.
+// An ordinary launch has the chip as soon, without the detour over the
+// runtime's queue for cooperative kernels, after whose first use events between
+// the process's streams cost several times more.
+hipError_t launch_waiting(const void *f, void **args, size_t lds, hipStream_t st, bool together);
 // Whether the current device is the 256-CU gfx950 with cooperative launches
 // that the row-split kernels count on.
 bool split_chip_ok();
@@ -281,8 +289,8 @@ hipError_t rank2_split_f32_configure();
 // Asv; ws: rank2_rsplit_ws_bytes.  mode 0: plain run; 1: traced (a.vtr, a.str
 // or null, with a.c and a.y); 2, not with `pairs`: adjoint (as
 // launch_rank2_split).  Dual: r0 traced and r1 adjoint side by side, not with
-// `pairs`.  `runs`: whether that many fit in one launch.  Cooperative; not for
-// graph capture.  With rep, a run whose waits ran out has written no V, S or
+// `pairs`.  `runs`: whether that many fit in one launch.  Not for graph
+// capture.  With rep, a run whose waits ran out has written no V, S or
 // sums (its traces are undefined), records no time-out, and is repeated by a
 // launch of other kernels with *rep behind it; without, it records
 // ROM_E_TIMEOUT in status and its results are invalid.

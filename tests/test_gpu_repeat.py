@@ -187,3 +187,42 @@ def test_runs_on_two_threads_default_streams(columns_table, state):
     for V, S in outs:
         assert torch.equal(V, ref[0]) and torch.equal(S, ref[1])
     rom.close()
+
+
+def test_row_split_runs_of_several_contexts_take_turns():
+    """Kernels whose workgroups wait for each other, from three threads on
+    streams of their own (FP64, FP32 column-block and row-split runs): each
+    gives what it gives alone, and no wait runs out (which takes about half a
+    second)."""
+    import threading
+    import time
+    jobs = []
+    for state, kv, ks, M, schedule in (("f64", 300, 280, 128, "auto"), ("f32", 300, 280, 100, "auto"),
+                                       ("f32", 512, 512, 100, "rowsplit")):
+        inst = synth.make_instance(kv, ks, M, seed=4, skew=kv == ks)
+        rom = _rom(inst, state, schedule)
+        mu = torch.tensor(inst["mu"], dtype=torch.float64, device="cuda")
+        ref = rom.zeros(M)
+        rom.run_rank2(mu, *ref, 200)
+        outs = [rom.zeros(M) for _ in range(15)]
+        jobs.append((rom, mu, ref, outs, torch.cuda.Stream()))
+    assert [_kernels(j[0]) for j in jobs] == [_lib.ROM_KERNEL_ROWS64, _lib.ROM_KERNEL_ROWS, 0]
+    torch.cuda.synchronize()
+
+    def run(rom, mu, ref, outs, stream):
+        for V, S in outs:
+            rom.run_rank2(mu, V, S, 200, stream=stream)
+
+    threads = [threading.Thread(target=run, args=j) for j in jobs]
+    t0 = time.perf_counter()
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert time.perf_counter() - t0 < 0.3
+    for rom, mu, ref, outs, stream in jobs:
+        rom.check()
+        for V, S in outs:
+            assert torch.equal(V, ref[0]) and torch.equal(S, ref[1])
+        rom.close()
