@@ -348,8 +348,9 @@ rom_status rom_check(rom_ctx *ctx, void *stream);
  * invalid results, and ROM_E_TIMEOUT is recorded.  The runs of other
  * schedules that take row-split kernels (FP32 column-block runs, FP64 runs)
  * are repeated on the column blocks and valid; the FP64 ones record
- * ROM_E_TIMEOUT all the same under this hook.  on = 0 restores normal waits.
- * Process-wide; returns ROM_OK.
+ * ROM_E_TIMEOUT all the same under this hook.  on = 2: no time-outs, but every
+ * other group of samples of those runs is treated as not done and repeated.
+ * on = 0 restores normal runs.  Process-wide; returns ROM_OK.
  */
 rom_status rom_debug_force_timeout(int32_t on);
 

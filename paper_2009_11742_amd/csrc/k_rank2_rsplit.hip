@@ -40,11 +40,12 @@ hipError_t fill(RArgs &a, const Tile *t, const void *opv, const void *ops, const
 
 // A repeatable run (rep): its groups' words are the flags, which these kernels
 // do not use, its status words are its own, behind the slot counters.
-void repeatable(RArgs &a, const Tile *t, Repeat *rep) {
-    if (!rep) return;
+hipError_t repeatable(RArgs &a, const Tile *t, Repeat *rep, hipStream_t st) {
+    if (!rep) return hipSuccess;
     a.s.done = a.s.flags;
     a.s.status = reinterpret_cast<int *>(a.s.slots + 8);
     *rep = Repeat{a.s.done, 16 * t->ncb, a.s.G};
+    return g_forced_timeout == 2 ? freeze_odd_groups(a.s.done, a.s.G, st) : hipSuccess;
 }
 
 hipError_t launch(const void *f, RArgs &a0, RArgs &a1, hipStream_t st) {
@@ -87,8 +88,8 @@ hipError_t launch_rank2_rsplit(bool pairs, const void *opv, const void *ops, con
     const Tile *t = pick_tile(pairs, r2.kv, r2.ks, r2.kvp, r2.ksp, r2.M, 1);
     if (!t || !t->f[mode]) return hipErrorInvalidValue;
     RArgs a{}, none{};
-    const hipError_t e = fill(a, t, opv, ops, r2, ws, status, st);
-    repeatable(a, t, rep);
+    hipError_t e = fill(a, t, opv, ops, r2, ws, status, st);
+    if (e == hipSuccess) e = repeatable(a, t, rep, st);
     return e == hipSuccess ? launch(t->f[mode], a, none, st) : e;
 }
 

@@ -462,7 +462,18 @@ __global__ void split_clear_kernel(u4 *__restrict__ x, size_t n, unsigned *__res
     if (i0 == 0) status[2] = 0;
 }
 
+__global__ void freeze_odd_kernel(unsigned *done, int n) {
+    const int g = 2 * (int)threadIdx.x + 1;
+    if (g < n) done[2 * g + 1] = xch::kGivenUp;
+}
+
 }  // namespace
+
+hipError_t freeze_odd_groups(unsigned *done, int n, hipStream_t st) {
+    if (n > 2 * kThreads) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(freeze_odd_kernel, dim3(1), dim3(kThreads), 0, st, done, n);
+    return hipGetLastError();
+}
 
 size_t rank2_split_lds_bytes() {
     return sizeof(float) * ((size_t)2 * 2 * kCols * kLd + (size_t)kWaves * kCols * kLd + 2 * kRows);
@@ -517,8 +528,8 @@ hipError_t split_workspace(SplitArgs &a, void *ws, size_t xfloats, size_t ypd, b
     a.yp = reinterpret_cast<u64 *>(a.x + xch::kRing * xfloats);
     a.flags = reinterpret_cast<unsigned *>(a.yp + xch::kRing * ypd);
     a.slots = a.flags + kFlagWords;
-    a.spin_max = g_forced_timeout ? 256 : xch::kSpinMax;
-    a.forced = g_forced_timeout ? 1 : 0;
+    a.spin_max = g_forced_timeout == 1 ? 256 : xch::kSpinMax;
+    a.forced = g_forced_timeout == 1 ? 1 : 0;
     const size_t n = (poll_rows ? xfloats : 0) + 2 * ypd;      // 16-byte words
     u4 *from = reinterpret_cast<u4 *>(poll_rows ? ws : static_cast<void *>(a.yp));
     const int blocks = (int)(n / 256 < 64 ? 64 : (n / 256 > 1024 ? 1024 : n / 256));

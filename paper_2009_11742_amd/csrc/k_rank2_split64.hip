@@ -505,8 +505,8 @@ hipError_t launch_rank2_split64(const void *opv, const void *ops, const Rank2Arg
     a.S = static_cast<double *>(r2.S);
     a.J = r2.J;
     a.y = r2.y;
-    a.spin_max = g_forced_timeout ? 256 : xch::kSpinMax;
-    a.forced = g_forced_timeout ? 1 : 0;
+    a.spin_max = g_forced_timeout == 1 ? 256 : xch::kSpinMax;
+    a.forced = g_forced_timeout == 1 ? 1 : 0;
     a.kv = r2.kv;
     a.ks = r2.ks;
     a.M = r2.M;
@@ -524,11 +524,12 @@ hipError_t launch_rank2_split64(const void *opv, const void *ops, const Rank2Arg
     const size_t nx = (size_t)a.cap * xch::kRing * kNC * k->kp, ny = (size_t)a.cap * xch::kRing * kNC * (k->kp / 16);
     a.yp = a.x + nx;
     a.slots = reinterpret_cast<unsigned *>(a.yp + ny);
-    a.status = g_forced_timeout ? status : reinterpret_cast<int *>(a.slots + 8);
+    a.status = g_forced_timeout == 1 ? status : reinterpret_cast<int *>(a.slots + 8);
     a.done = a.slots + 16;
     rep = Repeat{a.done, kNC, a.cap};
     hipLaunchKernelGGL(clear64_kernel, dim3(256), dim3(256), 0, st, a.x, nx + ny, a.slots, status);
     hipError_t e = hipGetLastError();
+    if (e == hipSuccess && g_forced_timeout == 2) e = freeze_odd_groups(a.done, a.cap, st);
     if (e != hipSuccess) return e;
     void *args[] = {&a};
     static_assert(kT == 256 && kXcd * kCuXcd == 256, "launch_waiting");

@@ -41,7 +41,7 @@ rom_status hip_fail(hipError_t e, const char *where) {
 }  // namespace
 
 namespace rom {
-bool g_forced_timeout = false;
+int g_forced_timeout = 0;
 rom_status api_fail(rom_status s, const std::string &msg) { return fail(s, msg); }
 rom_status api_hip_fail(hipError_t e, const char *where) { return hip_fail(e, where); }
 }  // namespace rom
@@ -999,7 +999,7 @@ rom_status rom_destroy(rom_ctx *ctx) {
 }
 
 rom_status rom_debug_force_timeout(int32_t on) {
-    rom::g_forced_timeout = on != 0;
+    rom::g_forced_timeout = on == 2 ? 2 : on != 0;
     return ROM_OK;
 }
 

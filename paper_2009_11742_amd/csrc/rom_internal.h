@@ -25,11 +25,12 @@ constexpr int kMaxSplitK = 2048;
 
 inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
-// Failure-handling test hook (rom_debug_force_timeout): when set, every
-// bounded in-kernel wait of the row-split kernels waits for one arrival too
-// many with a short poll budget, so it runs out and reports ROM_E_TIMEOUT
-// while the kernel still ends normally.
-extern bool g_forced_timeout;
+// Failure-handling test hook (rom_debug_force_timeout): with 1, every bounded
+// in-kernel wait for rows of the row-split kernels treats them as missing, with
+// a short poll budget, so it runs out and reports ROM_E_TIMEOUT while the
+// kernel still ends normally; with 2, every other group of the runs that can be
+// repeated is given up before it starts (freeze_odd_groups).
+extern int g_forced_timeout;
 
 }  // namespace rom
 
@@ -206,6 +207,8 @@ hipError_t launch_rank2_short64(const void *opv, const void *ops, const Rank2Arg
 // runtime's queue for cooperative kernels, after whose first use events between
 // the process's streams cost several times more.
 hipError_t launch_waiting(const void *f, void **args, size_t lds, hipStream_t st, bool together);
+// Test hook: the odd groups (slots) of n, their words at `done`, given up.
+hipError_t freeze_odd_groups(unsigned *done, int n, hipStream_t st);
 // Whether the current device is the 256-CU gfx950 with cooperative launches
 // that the row-split kernels count on.
 bool split_chip_ok();

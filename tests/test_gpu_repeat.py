@@ -226,3 +226,30 @@ def test_row_split_runs_of_several_contexts_take_turns():
         for V, S in outs:
             assert torch.equal(V, ref[0]) and torch.equal(S, ref[1])
         rom.close()
+
+
+# (f64, 192, 192): 40 slots of one or two rounds each, 32-row tiles
+@pytest.mark.parametrize("state,kv,ks,M,nc,slots", [
+    ("f64", 160, 130, 100, 16, 7), ("f64", 192, 192, 1100, 16, 40), ("f32", 256, 256, 250, 16, 16),
+    ("f32", 320, 300, 600, 32, 19), ("f32", 700, 600, 120, 16, 8)])
+def test_some_groups_are_repeated(columns_table, state, kv, ks, M, nc, slots):
+    """Every other group (FP64: slot of groups) given up: its samples are the
+    column blocks', the others the row-split kernels' own."""
+    inst = _inst(kv, ks, M)
+    columns_table(kv, ks, M)
+    lib = _lib.load()
+    rom, pinned = _rom(inst, state), _rom(inst, state, "columns")
+    own, blocks = _run(rom, inst, M, 30), _run(pinned, inst, M, 30)
+    lib.rom_debug_force_timeout(2)
+    try:
+        got = _run(rom, inst, M, 30)
+    finally:
+        lib.rom_debug_force_timeout(0)
+    rom.check()
+    rom.close(); pinned.close()
+    odd = torch.tensor(np.arange(M) // nc % slots % 2 == 1, device="cuda")
+    for i, (g, o, b) in enumerate(zip(got, own, blocks)):
+        g, o, b = (x.T if i == 3 else x.reshape(M, -1) for x in (g, o, b))
+        assert torch.equal(g[odd], b[odd]) and torch.equal(g[~odd], o[~odd])
+    if state == "f64":          # (the two differ in their last bits)
+        assert not torch.equal(own[0][odd], blocks[0][odd])
