@@ -236,7 +236,7 @@ rom_status rom_destroy(rom_ctx *ctx);
  *                          both above 192 nor (256, 192) either way round:
  *                          one or four samples per workgroup, all of whose
  *                          32-term chains run side by side; bitwise equal,
- *                          J and y included.  max(Kv_pad, Ks_pad) in [256,
+ *                          J and y included.  max(Kv_pad, Ks_pad) in [192,
  *                          1024], not captured, all samples on the chip at
  *                          once and enough steps (K = 256: 10) for that to be
  *                          faster: row-split kernels that keep the operators

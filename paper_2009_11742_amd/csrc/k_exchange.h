@@ -39,6 +39,16 @@
 namespace rom {
 namespace xch {
 
+// A kernel's first argument, read where this is called: what only the end of a
+// run needs would otherwise be held, and spilled, across its step loop.
+template <class A>
+__device__ __forceinline__ const __attribute__((address_space(4))) A &args_here() {
+    typedef const __attribute__((address_space(4))) A Args;
+    Args *p = (Args *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *p;
+}
+
 // Where the rows a wave reads do not fit in its registers at once, polling
 // them one by one would put a branch and a wait into the pipelined loads;
 // there each publishing wave counts its phases in a flag word, stored after

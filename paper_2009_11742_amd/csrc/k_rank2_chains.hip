@@ -31,7 +31,6 @@
 // M = 1000 2.4 -> 0.91; (150, 130), M = 256 3.1 -> 1.25; (128, 256), M =
 // 1022 3.5 -> 1.75.
 #include "k_common.h"
-#include "k_exchange.h"
 #include "k_lane.h"
 #include "rom_internal.h"
 
@@ -315,7 +314,6 @@ void rank2_chains_kernel(Rank2Args a) {
     const int nt = blockDim.x, nw = nt >> 6;
     const int i = lane & 15, dr = lane >> 4;
     const int kv = a.kv, ks = a.ks, M = a.M, m0 = blockIdx.x * NS;
-    if (a.rep.done && xch::committed(a.rep, m0)) return;        // (a group's samples are whole workgroups)
     const double dt = a.dt;
     const float *src = static_cast<const float *>(MODE == kAdjoint ? a.c : a.b);
     const float *prb = static_cast<const float *>(MODE == kAdjoint ? a.b : a.c);

@@ -286,9 +286,16 @@ template <int MODE, int NS, int TR>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void rank2_f32_mfma_kernel(Rank2Args a) {
     extern __shared__ __align__(16) unsigned char smem[];
+    run_block<MODE, NS, TR>(a, blockIdx.x * NB * NS, smem);
+}
+
+// The columns that the run `rep` has not done (a group's are whole workgroups).
+template <int NS, int TR>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void rank2_f32_mfma_repeat_kernel(Rank2Args a, Repeat rep) {
+    extern __shared__ __align__(16) unsigned char smem[];
     const int col0 = blockIdx.x * NB * NS;
-    if (a.rep.done && xch::committed(a.rep, col0)) return;      // (a group's columns are whole workgroups)
-    run_block<MODE, NS, TR>(a, col0, smem);
+    if (!xch::committed(rep, col0)) run_block<kForward, NS, TR>(a, col0, smem);
 }
 
 // Grouped forward run: workgroup i advances the column block of instance
@@ -330,13 +337,20 @@ static bool traces_probe_ok(const Rank2Args &a, bool adjoint) {
     return adjoint ? (a.b != nullptr && a.ytr != nullptr) : (a.c != nullptr && a.y != nullptr);
 }
 
-hipError_t launch_rank2_f32_mfma(const Rank2Args &a, int nset, hipStream_t st) {
+hipError_t launch_rank2_f32_mfma(const Rank2Args &a, int nset, hipStream_t st, const Repeat *rep) {
     const int nc = NB * nset;
     const int blocks = (a.M + nc - 1) / nc;
     const size_t lds = rank2_f32_mfma_lds_bytes(a.kvp, a.ksp, nset);
     if (a.vtr) {   // state traces: one column set
         if (!traces_probe_ok(a, false) || nset != 1) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((rank2_f32_mfma_kernel<kForward, 1, kTraces>), dim3(blocks), dim3(kThreads), lds, st, a);
+        if (rep)
+            hipLaunchKernelGGL((rank2_f32_mfma_repeat_kernel<1, kTraces>), dim3(blocks), dim3(kThreads), lds, st, a, *rep);
+        else
+            hipLaunchKernelGGL((rank2_f32_mfma_kernel<kForward, 1, kTraces>), dim3(blocks), dim3(kThreads), lds, st, a);
+    } else if (rep && nset == 2) {
+        hipLaunchKernelGGL((rank2_f32_mfma_repeat_kernel<2, kNoTraces>), dim3(blocks), dim3(kThreads), lds, st, a, *rep);
+    } else if (rep) {
+        hipLaunchKernelGGL((rank2_f32_mfma_repeat_kernel<1, kNoTraces>), dim3(blocks), dim3(kThreads), lds, st, a, *rep);
     } else if (nset == 2) {
         hipLaunchKernelGGL((rank2_f32_mfma_kernel<kForward, 2, kNoTraces>), dim3(blocks), dim3(kThreads), lds, st,
                            a);
@@ -373,6 +387,9 @@ hipError_t launch_grouped_f32_mfma(const Rank2Args *inst_dev, const int2 *items_
 
 hipError_t rank2_f32_mfma_configure() {
     const void *fns[] = {(const void *)grouped_f32_mfma_kernel,
+                         (const void *)rank2_f32_mfma_repeat_kernel<1, kNoTraces>,
+                         (const void *)rank2_f32_mfma_repeat_kernel<2, kNoTraces>,
+                         (const void *)rank2_f32_mfma_repeat_kernel<1, kTraces>,
                          (const void *)rank2_f32_mfma_kernel<kForward, 1, kNoTraces>,
                          (const void *)rank2_f32_mfma_kernel<kForward, 2, kNoTraces>,
                          (const void *)rank2_f32_mfma_kernel<kForward, 1, kTraces>,

@@ -73,7 +73,9 @@ bool rank2_rsplit_applies(bool pairs, int kv, int ks, int kvp, int ksp, int M, i
 
 float rank2_rsplit_us(bool pairs, int kv, int ks, int kvp, int ksp, int M) {
     const Tile *t = M >= 1 ? pick_tile(pairs, kv, ks, kvp, ksp, M, 1) : nullptr;
-    return t ? t->us : INFINITY;
+    if (!t) return INFINITY;
+    const int kp = kvp > ksp ? kvp : ksp;
+    return t->us * (1.0f - 0.04f * (float)((256 * t->nch - kp) / 64));
 }
 
 // (rank2_split_workspace_bytes of the same padded size and 64-column groups
@@ -84,7 +86,8 @@ size_t rank2_rsplit_ws_bytes(int kvp, int ksp, int M) {
 
 hipError_t launch_rank2_rsplit(bool pairs, const void *opv, const void *ops, const Rank2Args &r2, void *ws, int *status,
                                hipStream_t st, int mode, Repeat *rep) {
-    if (r2.M < 1 || r2.nsteps < 1 || mode < kPlain || mode > kAdjoint) return hipErrorInvalidValue;
+    if (r2.M < 1 || r2.nsteps < 1 || mode < kPlain || mode > kAdjoint || pairs != (rep != nullptr))
+        return hipErrorInvalidValue;
     const Tile *t = pick_tile(pairs, r2.kv, r2.ks, r2.kvp, r2.ksp, r2.M, 1);
     if (!t || !t->f[mode]) return hipErrorInvalidValue;
     RArgs a{}, none{};

@@ -654,7 +654,7 @@ hipError_t launch_waiting(const void *f, void **args, size_t lds, hipStream_t st
     // (held until the launch is recorded: the next one, of any thread, waits
     // for this one)
     std::lock_guard<std::mutex> lk(mu);
-    e = last[dev] ? hipStreamWaitEvent(st, last[dev], 0) : hipEventCreateWithFlags(&last[dev], hipEventDisableTiming);
+    e = last[dev] ? hipStreamWaitEvent(st, last[dev], 0) : hipEventCreateWithFlags(&last[dev], hipEventDisableTiming | hipEventDisableSystemFence);
     if (e != hipSuccess) return e;
     const dim3 grid(kXcds * kCusPerXcd), block(kThreads);
     e = together ? hipLaunchCooperativeKernel(f, grid, block, args, lds, st) : hipLaunchKernel(f, grid, block, args, lds, st);

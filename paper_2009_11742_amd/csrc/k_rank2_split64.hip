@@ -76,16 +76,6 @@ struct Args64 {
     double dt;
 };
 
-// The kernel's arguments, read where this is called: what only the ends of a
-// round need would otherwise be held, and spilled, across the step loop (0.15
-// us per step at KP = 320).
-typedef const __attribute__((address_space(4))) Args64 KernArgs64;
-__device__ __forceinline__ KernArgs64 &args_here() {
-    KernArgs64 *p = (KernArgs64 *)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p));
-    return *p;
-}
-
 constexpr int ld64(int NT) { return 16 * NT + 2; }     // LDS column stride of the partials
 
 // A wave's partials of its NT 16-row tiles, to LDS: the first and the second
@@ -237,11 +227,11 @@ void rank2_split64_kernel(Args64 a) {
     };
 
     unsigned round = 0;
-    for (int g = slot; g < args_here().G; g += args_here().cap) {
+    for (int g = slot; g < xch::args_here<Args64>().G; g += xch::args_here<Args64>().cap) {
         const int col0 = g * kNC, fm = col0 + fj;
-        const bool fok = fm < args_here().M;
+        const bool fok = fm < xch::args_here<Args64>().M;
         double sv[NT], ss[NT];
-        KernArgs64 &in = args_here();
+        const auto &in = xch::args_here<Args64>();       // (held, they cost 0.15 us per step)
 #pragma unroll
         for (int e = 0; e < NT; ++e) {
             sv[e] = (fok && fr + 16 * e < in.kv) ? in.V[(size_t)fm * in.kv + fr + 16 * e] : 0.0;
@@ -311,7 +301,7 @@ void rank2_split64_kernel(Args64 a) {
                 if (a.y && l < kNC && col0 + l < a.M) a.y[(size_t)k * a.M + col0 + l] = y;
             }
         }
-        KernArgs64 &out = args_here();
+        const auto &out = xch::args_here<Args64>();
         if (!xch::agree(out.done + 2 * slot, out.R, round++, wait)) return;
 #pragma unroll
         for (int e = 0; e < NT; ++e) {

@@ -33,8 +33,7 @@ __device__ __forceinline__ float fma_t<float>(float a, float b, float c) { retur
 // agree bitwise.  (Four interleaved FMA chains per entry measured no faster
 // at K = 64 and slower at K = 128.)
 template <typename T, int RPL>
-__global__ __launch_bounds__(256) void rank2_valu_kernel(Rank2Args a, int ops_in_lds) {
-    extern __shared__ __align__(16) unsigned char smem[];
+__device__ __forceinline__ void valu_run(const Rank2Args &a, int ops_in_lds, unsigned char *smem) {
     const int kv = a.kv, ks = a.ks, kvp = a.kvp, ksp = a.ksp;
     T *V = reinterpret_cast<T *>(smem);                // [NB][kvp]
     T *S = V + NB * kvp;                                // [NB][ksp]
@@ -47,7 +46,6 @@ __global__ __launch_bounds__(256) void rank2_valu_kernel(Rank2Args a, int ops_in
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int col0 = blockIdx.x * NB;
-    if (a.rep.done && xch::committed(a.rep, col0)) return;      // (a group's columns are whole workgroups)
     const T *Vin = static_cast<const T *>(a.V);
     const T *Sin = static_cast<const T *>(a.S);
     const T *bv = static_cast<const T *>(a.b);
@@ -179,6 +177,19 @@ __global__ __launch_bounds__(256) void rank2_valu_kernel(Rank2Args a, int ops_in
     if (cv != nullptr && a.J && lane == 0 && col0 + w < a.M) a.J[col0 + w] += Jacc;
 }
 
+template <typename T, int RPL>
+__global__ __launch_bounds__(256) void rank2_valu_kernel(Rank2Args a, int ops_in_lds) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    valu_run<T, RPL>(a, ops_in_lds, smem);
+}
+
+// The columns that the run `rep` has not done (a group's are whole workgroups).
+template <typename T, int RPL>
+__global__ __launch_bounds__(256) void rank2_valu_repeat_kernel(Rank2Args a, int ops_in_lds, Repeat rep) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    if (!xch::committed(rep, blockIdx.x * NB)) valu_run<T, RPL>(a, ops_in_lds, smem);
+}
+
 template <typename T>
 size_t valu_lds(int kv, int ks, int kvp, int ksp, bool ops) {
     size_t base = sizeof(T) * (size_t)NB * (kvp + ksp) + sizeof(double) * kUWinV * NB;
@@ -189,13 +200,18 @@ size_t valu_lds(int kv, int ks, int kvp, int ksp, bool ops) {
 }  // namespace
 
 template <typename T>
-hipError_t launch_rank2_valu(const Rank2Args &a, hipStream_t st) {
+hipError_t launch_rank2_valu(const Rank2Args &a, hipStream_t st, const Repeat *rep) {
     const int blocks = (a.M + NB - 1) / NB;
     bool ops = valu_lds<T>(a.kv, a.ks, a.kvp, a.ksp, true) <= kLdsBudget;
     size_t lds = valu_lds<T>(a.kv, a.ks, a.kvp, a.ksp, ops);
     if (lds > kLdsBudget) return hipErrorInvalidValue;
     const int kmax = a.kv > a.ks ? a.kv : a.ks;
-    if (kmax <= 64)
+    if (rep && (sizeof(T) != 8 || kmax <= 64)) return hipErrorInvalidValue;
+    if (rep && kmax <= 128)
+        hipLaunchKernelGGL((rank2_valu_repeat_kernel<T, 2>), dim3(blocks), dim3(256), lds, st, a, ops ? 1 : 0, *rep);
+    else if (rep)
+        hipLaunchKernelGGL((rank2_valu_repeat_kernel<T, 0>), dim3(blocks), dim3(256), lds, st, a, ops ? 1 : 0, *rep);
+    else if (kmax <= 64)
         hipLaunchKernelGGL((rank2_valu_kernel<T, 1>), dim3(blocks), dim3(256), lds, st, a, ops ? 1 : 0);
     else if (kmax <= 128)
         hipLaunchKernelGGL((rank2_valu_kernel<T, 2>), dim3(blocks), dim3(256), lds, st, a, ops ? 1 : 0);
@@ -204,8 +220,8 @@ hipError_t launch_rank2_valu(const Rank2Args &a, hipStream_t st) {
     return hipGetLastError();
 }
 
-template hipError_t launch_rank2_valu<double>(const Rank2Args &, hipStream_t);
-template hipError_t launch_rank2_valu<float>(const Rank2Args &, hipStream_t);
+template hipError_t launch_rank2_valu<double>(const Rank2Args &, hipStream_t, const Repeat *);
+template hipError_t launch_rank2_valu<float>(const Rank2Args &, hipStream_t, const Repeat *);
 
 size_t rank2_valu_lds_bytes(rom_dtype st, int kv, int ks, int kvp, int ksp) {
     return st == ROM_F64 ? valu_lds<double>(kv, ks, kvp, ksp, false)
@@ -213,7 +229,8 @@ size_t rank2_valu_lds_bytes(rom_dtype st, int kv, int ks, int kvp, int ksp) {
 }
 
 hipError_t rank2_valu_configure() {
-    const void *fns[] = {(const void *)rank2_valu_kernel<double, 0>, (const void *)rank2_valu_kernel<double, 1>,
+    const void *fns[] = {(const void *)rank2_valu_repeat_kernel<double, 0>, (const void *)rank2_valu_repeat_kernel<double, 2>,
+                         (const void *)rank2_valu_kernel<double, 0>, (const void *)rank2_valu_kernel<double, 1>,
                          (const void *)rank2_valu_kernel<double, 2>, (const void *)rank2_valu_kernel<float, 0>,
                          (const void *)rank2_valu_kernel<float, 1>, (const void *)rank2_valu_kernel<float, 2>};
     for (const void *f : fns) {

@@ -363,9 +363,9 @@ rom_status run_split64(rom_ctx *ctx, const rom::Rank2Args &a, hipStream_t st, bo
         if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
         return work ? sp_done(ctx, st) : ROM_OK;
     }
-    rom::Rank2Args again = a;
-    hipError_t e = rom::launch_rank2_split64(ctx->avs_sp, ctx->asv_sp, a, ctx->sp_ws, ctx->status, st, again.rep);
-    if (e == hipSuccess) e = rom::launch_rank2_valu<double>(again, st);
+    rom::Repeat rep;
+    hipError_t e = rom::launch_rank2_split64(ctx->avs_sp, ctx->asv_sp, a, ctx->sp_ws, ctx->status, st, rep);
+    if (e == hipSuccess) e = rom::launch_rank2_valu<double>(a, st, &rep);
     if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
     return sp_done(ctx, st);
 }
@@ -382,21 +382,23 @@ bool chains(const rom_ctx *ctx, int M) {
 // `launches` of them side by side.
 hipError_t launch_columns(rom_ctx *ctx, const rom::Rank2Args &a, int nset, bool adjoint, hipStream_t st,
                           int launches = 1) {
-    if (!a.rep.done) ctx->kernels |= chains(ctx, a.M) ? ROM_KERNEL_CHAINS : ROM_KERNEL_COLUMNS;
+    ctx->kernels |= chains(ctx, a.M) ? ROM_KERNEL_CHAINS : ROM_KERNEL_COLUMNS;
     if (chains(ctx, a.M)) return rom::launch_rank2_chains(a, adjoint, launches, st);
     return adjoint ? rom::launch_adjoint_f32_mfma(a, st) : rom::launch_rank2_f32_mfma(a, nset, st);
 }
 
 // Whether the resident row-split kernels, which compute the same sums, step a
 // column-block run of M samples faster than the column blocks or the small
-// models' kernels: FP32 operators, above 192 padded rows (up to there the
-// small models' kernels are faster than any tile), where all groups fit on the
-// chip at once and their measured step is shorter (K = 256 with a probe, M =
-// 256 2.6 us against 4.5, M = 512 3.6; above, groups of twice the columns take
-// 6.0), unless the context pins the column blocks.  In us per step, 0 if not.
+// models' kernels: FP32 operators, from 192 padded rows on (at 192 only where
+// the 16 x 16 tile holds more than the 256 samples that the small models'
+// kernels take one by one: up to 160 rows, 384 samples), where all groups fit
+// on the chip at once and their measured step is shorter (K = 256 with a probe,
+// M = 256 2.5 us against 4.5, M = 512 3.5; above, groups of twice the columns
+// take 6.0), unless the context pins the column blocks.  In us per step, 0 if
+// not.
 float rsplit_gain(const rom_ctx *ctx, int M) {
     if (!ctx->avs_sp || ctx->op_type != ROM_F32 || ctx->state_type != ROM_F32 ||
-        (ctx->flags & (ROM_SCHED_COLUMNS | ROM_SCHED_COLUMNS8)) || std::max(ctx->kvp, ctx->ksp) <= 192)
+        (ctx->flags & (ROM_SCHED_COLUMNS | ROM_SCHED_COLUMNS8)) || std::max(ctx->kvp, ctx->ksp) < 192)
         return 0.f;
     const float cols = chains(ctx, M) ? rom::rank2_chains_us(ctx->kvp, ctx->ksp, M)
                                       : rom::rank2_f32_mfma_us(ctx->kvp, ctx->ksp);
@@ -420,10 +422,12 @@ bool rsplit_columns(rom_ctx *ctx, int M, int64_t nsteps, hipStream_t st) {
 // `again`: its arguments on the column blocks (nset column sets), which do
 // behind it what a time-out left undone (otherwise a look at one word per
 // group).
-rom_status run_rsplit_columns(rom_ctx *ctx, const rom::Rank2Args &a, rom::Rank2Args again, int nset, hipStream_t st) {
+rom_status run_rsplit_columns(rom_ctx *ctx, const rom::Rank2Args &a, const rom::Rank2Args &again, int nset,
+                              hipStream_t st) {
+    rom::Repeat rep;
     hipError_t e = rom::launch_rank2_rsplit(true, ctx->avs_sp, ctx->asv_sp, a, ctx->sp_ws, ctx->status, st,
-                                            a.vtr ? 1 : 0, &again.rep);
-    if (e == hipSuccess) e = launch_columns(ctx, again, nset, false, st);
+                                            a.vtr ? 1 : 0, &rep);
+    if (e == hipSuccess) e = rom::launch_rank2_f32_mfma(again, nset, st, &rep);
     if (e != hipSuccess) return hip_fail(e, "rom_run_rank2: launch");
     ctx->kernels |= ROM_KERNEL_ROWS;
     return sp_done(ctx, st);
@@ -790,7 +794,7 @@ rom_status build_ctx(const rom_config *cfg, bool skew, const double *sA, const d
                                           st), ": pack");
         }
     }
-    if (c->state_type == ROM_F32 && split_candidate(c, 1) == 0 && !lowp && std::max(c->kvp, c->ksp) > 192 &&
+    if (c->state_type == ROM_F32 && split_candidate(c, 1) == 0 && !lowp && std::max(c->kvp, c->ksp) >= 192 &&
         rom::rank2_rsplit_applies(true, kv, ks, c->kvp, c->ksp, 1, 1) && split_device(c)) {
         // Kv != Ks: the packs of the resident row-split kernels (without the
         // memory for them the column blocks run)
@@ -1644,7 +1648,7 @@ rom_status rom_run_receivers(rom_ctx *ctx, int32_t M, const double *mu, int64_t 
     // after the side stream has read it.
     hipStream_t s2 = ctx->side[0];
     rom::Rank2Args a;
-    const bool rsplit = rsplit_columns(ctx, M, std::min(L, nsteps), st), blocks = !chains(ctx, M);
+    const bool rsplit = rsplit_columns(ctx, M, std::min(L, nsteps), st), blocks = rsplit || !chains(ctx, M);
     a.b = ctx->b; a.c = nullptr; a.y = nullptr; a.mu = mu; a.V = V; a.S = S; a.J = nullptr;
     a.kv = kv; a.ks = ks; a.kvp = ctx->kvp; a.ksp = ctx->ksp; a.M = M; a.dt = ctx->dt; a.source = ctx_source(ctx);
     a.avs = ctx->avs_pk; a.asv = ctx->asv_pk;

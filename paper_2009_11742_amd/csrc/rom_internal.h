@@ -117,10 +117,10 @@ namespace rom {
 
 // What a launch that repeats a row-split run needs to know of it: group g of
 // nc samples was round g / slots of slot g % slots, whose two words tell the
-// rounds done (k_exchange.h).  done null: not a repeat.
+// rounds done (k_exchange.h).
 struct Repeat {
-    const unsigned *done = nullptr;
-    int nc = 1, slots = 1;
+    const unsigned *done;
+    int nc, slots;
 };
 
 struct Rank2Args {
@@ -150,9 +150,6 @@ struct Rank2Args {
     // BF16 / FP8 operators: 1 = the state enters the products as bf16(x)
     // alone (one MFMA pass), 0 = as the BF16 pair (x_hi, x_lo)
     int single = 0;
-    // column blocks and small models: samples that an earlier run has done
-    // are left alone
-    Repeat rep;
 };
 
 // Operator-resident kernel (skew pairs, FP32): whether padded sizes fit it,
@@ -225,7 +222,8 @@ float rank2_chains_us(int kvp, int ksp, int M);
 hipError_t launch_rank2_chains(const Rank2Args &a, bool adjoint, int launches, hipStream_t st);
 
 // Launchers (return hipSuccess or the launch error).
-hipError_t launch_rank2_f32_mfma(const Rank2Args &a, int nset, hipStream_t st);
+// rep: samples that the run it names has done are left alone.
+hipError_t launch_rank2_f32_mfma(const Rank2Args &a, int nset, hipStream_t st, const Repeat *rep = nullptr);
 size_t rank2_f32_mfma_lds_bytes(int kvp, int ksp, int nset);
 float rank2_f32_mfma_us(int kvp, int ksp);
 hipError_t launch_adjoint_f32_mfma(const Rank2Args &a, hipStream_t st);
@@ -293,9 +291,9 @@ hipError_t rank2_split_f32_configure();
 // or null, with a.c and a.y); 2, not with `pairs`: adjoint (as
 // launch_rank2_split).  Dual: r0 traced and r1 adjoint side by side, not with
 // `pairs`.  `runs`: whether that many fit in one launch.  Not for graph
-// capture.  With rep, a run whose waits ran out has written no V, S or
+// capture.  Pairs with rep: a run whose waits ran out has written no V, S or
 // sums (its traces are undefined), records no time-out, and is repeated by a
-// launch of other kernels with *rep behind it; without, it records
+// launch of other kernels with *rep behind it.  Quarters without: it records
 // ROM_E_TIMEOUT in status and its results are invalid.
 bool rank2_rsplit_applies(bool pairs, int kv, int ks, int kvp, int ksp, int M, int runs);
 // Its step in us, as measured for the tile it takes; infinity if none fits.
@@ -338,7 +336,7 @@ hipError_t launch_energy(const double *A64, int kv, int ks, double dt, rom_dtype
 hipError_t launch_pack_f32_from_f32(const float *A, int rows, int cols, bool transpose, int prow,
                                     int pcol, float *pk, hipStream_t st);
 template <typename T>
-hipError_t launch_rank2_valu(const Rank2Args &a, hipStream_t st);
+hipError_t launch_rank2_valu(const Rank2Args &a, hipStream_t st, const Repeat *rep = nullptr);
 
 template <typename T>
 hipError_t launch_rank1_step(const void *avs_cm, const void *asv_cm, const void *b, int kv,

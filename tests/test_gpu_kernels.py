@@ -46,9 +46,9 @@ def _launched(kv, ks, M, state, schedule="auto", call="run", N=200):
 
 
 CHAINS = [(1, 1, 1), (64, 63, 257), (113, 128, 1001), (192, 128, 40), (131, 190, 300), (256, 64, 260), (70, 193, 300),
-          # 192 padded rows: no row-split tile is faster
-          (192, 130, 1), (130, 192, 17), (192, 192, 700)]
-ROWS = [(256, 192, 20), (192, 256, 300), (256, 200, 128), (250, 256, 500), (256, 256, 512), (300, 280, 33),
+          # 192 padded rows: few or many samples, or more than 160 rows
+          (150, 130, 200), (150, 130, 385), (192, 130, 1), (130, 192, 17), (192, 192, 700)]
+ROWS = [(150, 130, 300), (160, 129, 384), (256, 192, 20), (192, 256, 300), (256, 200, 128), (250, 256, 500), (256, 256, 512), (300, 280, 33),
         (64, 512, 16), (512, 500, 129), (512, 512, 500), (700, 600, 128), (600, 768, 250),
         (1000, 1024, 100), (1024, 900, 256)]
 # No tile that holds all their groups is faster.
