@@ -646,7 +646,9 @@ hipError_t launch_rank2_split(const void *opv, const void *ops, const Rank2Args 
 hipError_t launch_waiting(const void *f, void **args, size_t lds, hipStream_t st, bool together) {
     constexpr int kMaxDevices = 64;
     static std::mutex mu;
-    static hipEvent_t last[kMaxDevices] = {};      // behind the device's last such launch
+    // behind the device's last such launch; it orders kernels and hands no data
+    // on (contexts guard their workspaces), so its record releases no caches
+    static hipEvent_t last[kMaxDevices] = {};
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -654,7 +656,8 @@ hipError_t launch_waiting(const void *f, void **args, size_t lds, hipStream_t st
     // (held until the launch is recorded: the next one, of any thread, waits
     // for this one)
     std::lock_guard<std::mutex> lk(mu);
-    e = last[dev] ? hipStreamWaitEvent(st, last[dev], 0) : hipEventCreateWithFlags(&last[dev], hipEventDisableTiming | hipEventDisableSystemFence);
+    e = last[dev] ? hipStreamWaitEvent(st, last[dev], 0)
+                  : hipEventCreateWithFlags(&last[dev], hipEventDisableTiming | hipEventDisableSystemFence);
     if (e != hipSuccess) return e;
     const dim3 grid(kXcds * kCusPerXcd), block(kThreads);
     e = together ? hipLaunchCooperativeKernel(f, grid, block, args, lds, st) : hipLaunchKernel(f, grid, block, args, lds, st);

@@ -212,7 +212,7 @@ rom_status prepare_split_pack(rom_ctx *ctx, hipStream_t st) {
 rom_status take_sp_ws(rom_ctx *ctx, size_t need, hipStream_t st) {
     hipError_t e;
     if (!ctx->sp_ev) {
-        e = hipEventCreateWithFlags(&ctx->sp_ev, hipEventDisableTiming);
+        e = hipEventCreateWithFlags(&ctx->sp_ev, hipEventDisableTiming | hipEventReleaseToDevice);
         if (e != hipSuccess) { ctx->sp_ev = nullptr; return hip_fail(e, "rom_run_rank2: event creation"); }
     } else {
         e = hipStreamWaitEvent(st, ctx->sp_ev, 0);
