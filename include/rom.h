@@ -526,10 +526,14 @@ rom_status rom_run_rank2_noalloc(rom_ctx *ctx, int32_t M, const double *mu, int6
  * on `stream` (the context then also keeps row-split packs of Asv^T and
  * Avs^T, 2 K^2 floats), the call synchronises `stream` at its end and
  * returns ROM_E_TIMEOUT if a group exchange of those sweeps timed out.
- * Otherwise the recompute of the next segment runs on an internal stream
- * beside the reverse sweep on `stream`, and the gradient products of a
- * reversed segment on a second one (with row-split sweeps on `stream`, the
- * launches taking turns on the chip); the context keeps the
+ * The gradient products of a reversed segment then take turns with them.
+ * Otherwise the call synchronises `stream` only where it tunes the shape or
+ * allocates workspace.  The sweeps of small models (Kv_pad,
+ * Ks_pad as for the small models' kernels of ROM_SCHEDULE_COLUMNS8) and their
+ * products run on `stream` one after the other; of others, and with
+ * ckpt_stride = -1, the recompute of the next segment runs on an internal
+ * stream beside the reverse sweep on `stream`, and the gradient products of a
+ * reversed segment on a second one.  The context keeps the
  * workspace (checkpoints unless ckpt_stride = -1, three sets of state and
  * probe traces, two of W/Q traces: about 0.45 GB at Kv = Ks = 512, M = 256,
  * N = 5000, 0.07 GB less without checkpoints) until rom_destroy.
