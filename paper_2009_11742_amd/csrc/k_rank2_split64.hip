@@ -37,8 +37,8 @@
 // (RT = 32) at KP = 320; the exchange (store to L2, poll, load), about
 // 0.8 us, and the LDS meeting of the waves are the rest.  Measured (us per
 // step, this schedule / the vector-ALU column blocks): (300, 280) M = 128
-// 3.6 / 80; (128, 128) non-skew M = 3 2.0 / 14.5; (192, 192) M = 700 7.7
-// (two rounds); (320, 320) M = 900 15.5 (three rounds).  The probe costs
+// 3.6 / 80; (128, 128) non-skew M = 3 2.0 / 14.5; (192, 192) M = 700 7.3
+// (two rounds); (320, 320) M = 900 14.7 (three rounds).  The probe costs
 // nothing measurable: its sum runs while row tile 0 would wait for the next
 // rows (read before the stress half-step, it took 0.8 us of the step).
 #include "k_common.h"
